@@ -7,16 +7,17 @@
 //   TN  C[M,N] = A[K,M]^T B[K,N]   weight gradients dy^T x over K = tokens,
 //                                  accumulated into f32 (+=)
 //
-// Both operands are staged in LDS K-contiguous ([rows][BK + pad]) so that
-// every lane reads its MFMA fragment with one 16-byte LDS read.  Operands
-// that are contiguous along M or N in memory are transposed on the way in:
-// each thread loads a VEC x VEC block with VEC 16-byte loads and writes it
-// back as VEC 16-byte LDS rows.  The K loop is sequential, so every output
-// element sums its products in the same order whatever the tile shape:
-// results depend only on (M, N, K) and the data.
+// bf16 products whose operands are 16-byte aligned take the direct-to-LDS
+// kernel of gemm_quad.h.  The kernel here serves f32 and everything else: both
+// operands are staged in LDS K-contiguous ([rows][BK + pad]) so that every lane
+// reads its MFMA fragment with one 16-byte LDS read, and operands that are
+// contiguous along M or N in memory are transposed on the way in: each thread
+// loads a VEC x VEC block with VEC 16-byte loads and writes it back as VEC
+// 16-byte LDS rows.  The K loop is sequential: results depend only on (M, N,
+// K), the alignment and the data.
 #pragma once
 #include <type_traits>
-#include "gemm_pipe.h"
+#include "gemm_quad.h"
 #include "kernels.h"
 #include "tps_device.h"
 
@@ -246,12 +247,34 @@ static hipError_t launch_tile(GemmArgs g, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <int LAYOUT, int EPI>
+static hipError_t launch_bf16(bool big, const GemmArgs& g, hipStream_t stream) {
+  return big ? launch_quad<LAYOUT, 256, 256, 2, 4, 2, EPI>(g, stream)
+             : launch_quad<LAYOUT, 128, 128, 2, 2, 2, EPI>(g, stream);
+}
+
 template <int LAYOUT>
 static hipError_t launch_layout(int dtype, GemmArgs g, hipStream_t stream) {
   const GemmTile t = gemm_select_tile(dtype, LAYOUT, g);
-  if (t.aligned) {
-    if (t.bm == 256) return launch_pipe<LAYOUT, 256, 256>(g, stream);
-    return launch_pipe<LAYOUT, 128, 128>(g, stream);
+  if (t.fast) {
+    // the epilogues each layout uses in the stage (others take the generic path)
+    const bool big = t.bm == 256;
+    if constexpr (LAYOUT == TPS_GEMM_NT) {
+      switch (g.epi) {
+        case TPS_EPI_BIAS: return launch_bf16<LAYOUT, TPS_EPI_BIAS>(big, g, stream);
+        case TPS_EPI_BIAS_RESID: return launch_bf16<LAYOUT, TPS_EPI_BIAS_RESID>(big, g, stream);
+        case TPS_EPI_BIAS_GELU: return launch_bf16<LAYOUT, TPS_EPI_BIAS_GELU>(big, g, stream);
+        case TPS_EPI_GELU_GRAD: return launch_bf16<LAYOUT, TPS_EPI_GELU_GRAD>(big, g, stream);
+        default: return launch_bf16<LAYOUT, TPS_EPI_STORE>(big, g, stream);
+      }
+    } else if constexpr (LAYOUT == TPS_GEMM_NN) {
+      if (g.epi == TPS_EPI_GELU_GRAD) return launch_bf16<LAYOUT, TPS_EPI_GELU_GRAD>(big, g, stream);
+      if (g.epi == TPS_EPI_BIAS_RESID) return launch_bf16<LAYOUT, TPS_EPI_BIAS_RESID>(big, g, stream);
+      return launch_bf16<LAYOUT, TPS_EPI_STORE>(big, g, stream);
+    } else {
+      if (g.epi == TPS_EPI_ACC_F32) return launch_bf16<LAYOUT, TPS_EPI_ACC_F32>(big, g, stream);
+      return launch_bf16<LAYOUT, TPS_EPI_STORE>(big, g, stream);
+    }
   }
   if (dtype == TPS_BF16) {
     if (t.bm == 256) return launch_tile<bf16, 256, 128, 64, LAYOUT>(g, stream);

@@ -1,17 +1,6 @@
-// Building blocks of the bf16 GEMMs on gfx950 (gemm_pipe.h):
-//
-// LDS tile layouts.  Operand tiles are stored in their natural memory layout:
-//   K-contiguous operand (A of NT/NN, B of NT): [rows][BK] bf16;
-//   M/N-contiguous operand (A of TN, B of NN/TN): [BK][rows] bf16.
-// 16-byte chunks are XOR-swizzled within a row (the global address of each
-// lane is permuted so the chunk lands at its swizzled slot), which keeps the
-// fragment reads free of LDS bank conflicts:
-//   K-contiguous: ds_read_b128 gives a lane 8 consecutive k of one row;
-//   M/N-contiguous: two ds_read_b64_tr_b16 give a lane 8 consecutive k of one
-//   column (the read transposes 4 x 4 blocks of 16-bit values across lanes).
-//
-// Fragment reads are issued as inline assembly with explicit waits (see
-// below), and the epilogue parks accumulators in LDS to apply bias /
+// Building blocks of the bf16 GEMM (gemm_quad.h) and the attention kernels on
+// gfx950: LDS fragment reads issued as inline assembly with explicit waits,
+// and the GEMM epilogue, which parks accumulators in LDS to apply bias /
 // residual / GeLU / GeLU' / f32 accumulation with 16-byte accesses.
 #pragma once
 #include <utility>
@@ -26,56 +15,10 @@ namespace gl {
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-// Byte offset of chunk c (16 bytes) of row r in a K-contiguous tile with BK
-// columns.  ds_read_b128 serves 16 lanes = 16 consecutive rows at one chunk
-// per pass; the swizzle spreads them over all 64 banks:
-//   BK = 64 (128-byte rows, odd rows in the other bank half): c ^ ((r >> 1) & 7);
-//   BK = 32 (64-byte rows, four rows per 256 bytes): c ^ ((r >> 2) & 3).
-template <int BK>
-__device__ __forceinline__ int kc_off(int r, int c) {
-  if constexpr (BK == 64) return r * 128 + ((c ^ ((r >> 1) & 7)) << 4);
-  else return r * 64 + ((c ^ ((r >> 2) & 3)) << 4);
-}
-// Byte offset of chunk c of row r in an M/N-contiguous tile with ROWB-byte rows
-// (ROWB >= 256).  A pass of ds_read_tr16_b64 serves 32 lanes reading 4 rows x
-// 4 chunks; XOR-ing chunk bits 2-3 with the row puts the 16 chunks on 16
-// different bank groups.
-template <int ROWB>
-__device__ __forceinline__ int mc_off(int r, int c) { return r * ROWB + ((c ^ ((r & 3) << 2)) << 4); }
-
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt");
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// Issue the direct-to-LDS loads of one operand tile.  ROWS = tile extent along
-// M or N.  KC: operand is K-contiguous (global [rows][ld], tile rows x 64);
-// otherwise M/N-contiguous (global [k][ld], tile 64 x rows).
-template <int ROWS, bool KC, int NTHREADS, int BK>
-__device__ __forceinline__ void issue_tile(const bf16* g, int64_t ld, int row0, int k0, char* lds) {
-  constexpr int TILE_BYTES = ROWS * BK * 2;
-  constexpr int PER_WAVE = TILE_BYTES / 1024 / (NTHREADS / 64);   // 1 KB per wave instruction
-  static_assert(TILE_BYTES % (1024 * (NTHREADS / 64)) == 0, "tile must split evenly over waves");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int i = 0; i < PER_WAVE; ++i) {
-    const int inst = wave * PER_WAVE + i;
-    const int slot = inst * 64 + lane;       // 16-byte slot in the tile
-    const bf16* src;
-    if constexpr (KC) {
-      constexpr int CPR = BK / 8;
-      const int r = slot / CPR, p = slot % CPR;
-      const int c = (BK == 64) ? (p ^ ((r >> 1) & 7)) : (p ^ ((r >> 2) & 3));
-      src = g + (int64_t)(row0 + r) * ld + k0 + c * 8;
-    } else {
-      constexpr int CPR = ROWS / 8;           // chunks per row
-      const int r = slot / CPR, p = slot % CPR;
-      const int c = p ^ ((r & 3) << 2);
-      src = g + (int64_t)(k0 + r) * ld + row0 + c * 8;
-    }
-    __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)(lds + inst * 1024), 16, 0, 0);
-  }
 }
 
 // LDS fragment reads are issued as inline assembly.  The compiler orders
@@ -110,36 +53,6 @@ __device__ __forceinline__ void pin(bf16x8& v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void pin(f32x4& v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
-// Per-lane LDS byte offsets of the fragments a wave reads from one stage,
-// for the KSW k-steps of 16 starting at k-step ks0 of the tile.
-//   K-contiguous: fragment i (row block i) of k-step ks sits at
-//     row (row_base + 32 i + lane % 32), chunk 2 ks + lane / 32; the row swizzle
-//     repeats every 32 rows, so only the chunk term depends on ks:
-//     off(i, ks) = base[ks] + 4096 i (BK = 64) or 2048 i (BK = 32).
-//   M/N-contiguous: fragment j of k-step ks is two transposing reads at
-//     k rows (16 ks + 8 (g / 2) + s / 4) and 4 further; the column swizzle
-//     depends on k mod 4 only, so off(j, ks) = base[j] + 16 (ks - ks0) ROWB.
-template <int ROWS, bool KC, int BK, int NF, int KSW>
-struct FragAddr {
-  uint32_t base[KC ? KSW : NF];
-  __device__ __forceinline__ void init(int row_base, int ks0, int lane) {
-    if constexpr (KC) {
-      const int r = row_base + (lane & 31);
-#pragma unroll
-      for (int kk = 0; kk < KSW; ++kk) base[kk] = kc_off<BK>(r, (ks0 + kk) * 2 + (lane >> 5));
-    } else {
-      constexpr int ROWB = ROWS * 2;
-      const int g = lane >> 4, s = lane & 15;
-      const int k = 16 * ks0 + ((g >> 1) << 3) + (s >> 2);
-#pragma unroll
-      for (int j = 0; j < NF; ++j) {
-        const int col = row_base + 32 * j + ((g & 1) << 4) + ((s & 3) << 2);
-        base[j] = mc_off<ROWB>(k, col >> 3) + (col & 7) * 2;
-      }
-    }
-  }
-};
-
 template <typename F, int... I>
 __device__ __forceinline__ void static_for_impl(F& f, std::integer_sequence<int, I...>) {
   (f(std::integral_constant<int, I>{}), ...);
@@ -148,56 +61,6 @@ __device__ __forceinline__ void static_for_impl(F& f, std::integer_sequence<int,
 template <int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-// LDS reads per fragment set (each transposed fragment takes two reads).
-template <bool KC, int NF>
-constexpr int frag_reads() { return KC ? NF : 2 * NF; }
-
-// Issue the LDS reads of the NF fragments of the wave's k-step KK from the
-// stage at LDS byte address `stage`.
-template <int ROWS, bool KC, int BK, int NF, int KSW, int KK>
-__device__ __forceinline__ void read_frags(bf16x8 (&f)[NF], const FragAddr<ROWS, KC, BK, NF, KSW>& a,
-                                           uint32_t stage) {
-  if constexpr (KC) {
-    constexpr int RS = BK * 64;   // bytes between row blocks of 32
-    const uint32_t p = stage + a.base[KK];
-    if constexpr (NF > 0) f[0] = ds_b128<0>(p);
-    if constexpr (NF > 1) f[1] = ds_b128<RS>(p);
-    if constexpr (NF > 2) f[2] = ds_b128<2 * RS>(p);
-    if constexpr (NF > 3) f[3] = ds_b128<3 * RS>(p);
-    static_assert(NF <= 4, "fragments per k-step");
-  } else {
-    constexpr int ROWB = ROWS * 2;
-    typedef __attribute__((ext_vector_type(8))) short s16x8;
-#pragma unroll
-    for (int j = 0; j < NF; ++j) {
-      const uint32_t p = stage + a.base[j];
-      const s16x4 lo = ds_tr16<16 * KK * ROWB>(p);
-      const s16x4 hi = ds_tr16<16 * KK * ROWB + 4 * ROWB>(p);
-      s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      f[j] = *reinterpret_cast<bf16x8*>(&v);
-    }
-  }
-}
-
-// Issue the LDS read(s) of fragment N alone of the wave's k-step KK.
-template <int ROWS, bool KC, int BK, int NF, int KSW, int KK, int N>
-__device__ __forceinline__ void read_frag(bf16x8 (&f)[NF], const FragAddr<ROWS, KC, BK, NF, KSW>& a,
-                                          uint32_t stage) {
-  static_assert(N < NF, "fragment index");
-  if constexpr (KC) {
-    constexpr int RS = BK * 64;   // bytes between row blocks of 32
-    f[N] = ds_b128<N * RS>(stage + a.base[KK]);
-  } else {
-    constexpr int ROWB = ROWS * 2;
-    typedef __attribute__((ext_vector_type(8))) short s16x8;
-    const uint32_t p = stage + a.base[N];
-    const s16x4 lo = ds_tr16<16 * KK * ROWB>(p);
-    const s16x4 hi = ds_tr16<16 * KK * ROWB + 4 * ROWB>(p);
-    s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    f[N] = *reinterpret_cast<bf16x8*>(&v);
-  }
 }
 
 }  // namespace gl
@@ -218,29 +81,36 @@ struct EpiIn {
   Vec16<bf16> v[(EPI == TPS_EPI_BIAS_RESID || EPI == TPS_EPI_GELU_GRAD) ? P : 1];
 };
 
-template <int EPI, int BM, int BN, int WGM, int WGN, int TM, int TN, int LDS_BYTES>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[TM][TN], char* smem, int m0, int n0,
-                                              int wm, int wn, int lane, int wave) {
-  constexpr int WM = BM / WGM, WN = BN / WGN;
-  constexpr int LDE = WN + 8;   // f32 row pitch (keeps the parking writes conflict-free)
-  static_assert(WGM * WGN * 32 * LDE * 4 <= LDS_BYTES, "epilogue staging must fit in LDS");
+// acc: 16 x 16 blocks [2 TA][4]; lane l holds row l % 16 and columns 4 (l / 16)
+// .. +4 of each.  Strip i is blocks 2 i and 2 i + 1 of the wave's rows.
+// row_of(i): output row of row 0 of strip i; col_of(c): output column of
+// column c of the wave's 64 (groups of 8 columns stay together).
+// RAGGED: rows at or past M and groups of 8 columns at or past N (N a multiple
+// of 8) are neither read nor written.
+template <int EPI, bool RAGGED, int NWAVES, int TA, int LDS_BYTES, typename RowOf, typename ColOf>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x4 (&acc)[2 * TA][4], char* smem, RowOf&& row_of,
+                                              ColOf&& col_of, int lane, int wave) {
+  constexpr int WN = 64, TM = TA;   // strips
+  constexpr int LDE = WN + 4;       // f32 row pitch: the parking writes are conflict-free, rows 16-byte aligned
+  static_assert(NWAVES * 32 * LDE * 4 <= LDS_BYTES, "epilogue staging must fit in LDS");
   float* strip = reinterpret_cast<float*>(smem) + wave * 32 * LDE;
   constexpr int CPR = WN / 8;             // 8-column chunks per row
   constexpr int RPP = 64 / CPR;           // rows per pass
   constexpr int P = 32 / RPP;             // passes per strip
   const int rl0 = lane / CPR, cl = (lane % CPR) * 8;
-  const int col = n0 + wn * WN + cl;
-  const int row0 = m0 + wm * WM + rl0;    // row of pass 0 of strip 0
+  const int col = col_of(cl);
+  const bool col_ok = !RAGGED || col < g.N;
+  auto ok = [&](int64_t row) { return !RAGGED || (col_ok && row < g.M); };
   Vec16<bf16> bias;
   if constexpr (EPI == TPS_EPI_BIAS || EPI == TPS_EPI_BIAS_RESID || EPI == TPS_EPI_BIAS_GELU)
-    bias = load16(static_cast<const bf16*>(g.bias) + col);
+    bias = col_ok ? load16(static_cast<const bf16*>(g.bias) + col) : zero16<bf16>();
 
   auto load_strip = [&](int i, EpiIn<EPI, P>& in) {
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-      const int64_t row = row0 + i * 32 + q * RPP;
+      const int64_t row = row_of(i) + rl0 + q * RPP;
       if constexpr (EPI == TPS_EPI_ACC_F32) {
-        if (g.overwrite) {
+        if (g.overwrite || !ok(row)) {
           in.c0[q] = f32x4{0.f, 0.f, 0.f, 0.f};
           in.c1[q] = f32x4{0.f, 0.f, 0.f, 0.f};
         } else {
@@ -249,9 +119,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[T
           in.c1[q] = c[1];
         }
       } else if constexpr (EPI == TPS_EPI_BIAS_RESID) {
-        in.v[q] = load16(static_cast<const bf16*>(g.resid) + row * g.ldr + col);
+        in.v[q] = ok(row) ? load16(static_cast<const bf16*>(g.resid) + row * g.ldr + col) : zero16<bf16>();
       } else if constexpr (EPI == TPS_EPI_GELU_GRAD) {
-        in.v[q] = load16(static_cast<const bf16*>(g.aux) + row * g.ldaux + col);
+        in.v[q] = ok(row) ? load16(static_cast<const bf16*>(g.aux) + row * g.ldaux + col) : zero16<bf16>();
       }
     }
   };
@@ -260,9 +130,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[T
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) strip[acc_row(r, lane) * LDE + j * 32 + (lane & 31)] = acc[i][j][r];
+      for (int j = 0; j < 4; ++j)
+        *reinterpret_cast<f32x4*>(strip + (b * 16 + (lane & 15)) * LDE + j * 16 + (lane >> 4) * 4) = acc[2 * i + b][j];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -274,7 +145,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[T
       const f32x4 v0 = *reinterpret_cast<const f32x4*>(strip + rl * LDE + cl);
       const f32x4 v1 = *reinterpret_cast<const f32x4*>(strip + rl * LDE + cl + 4);
       const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-      const int64_t row = row0 + i * 32 + q * RPP;
+      const int64_t row = row_of(i) + rl0 + q * RPP;
+      if (!ok(row)) continue;
       if constexpr (EPI == TPS_EPI_ACC_F32) {
         f32x4* c = reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + row * g.ldc + col);
         f32x4 c0 = cur.c0[q], c1 = cur.c1[q];

@@ -1,0 +1,413 @@
+// bf16 GEMM on BM x BN tiles, K tiles of 64, 16x16x32 MFMAs.
+//
+// What bounds it: at 256 x 256 the chip's power.  With random data the matrix
+// pipes pull the clock down from 2.4 GHz, so a product's rate is set by the
+// energy per flop as much as by the cycles it leaves idle: a loop of nothing
+// but MFMAs on N(0, 1) data ran at 1855 TFLOP/s with 32x32x16 and at 2094 with
+// 16x16x32 MFMAs (half the accumulator traffic per flop), both at 2420 on
+// zeros.
+//
+// The K loop.  The MFMAs of a 256 x 256 K tile take 2048 cycles per CU while 64
+// KB must arrive from L2 or beyond, so a tile's loads must be issued well over
+// one K tile ahead; a ring of two whole tiles (128 KB of the 160 KB LDS) cannot
+// do that when a stage is refilled only after the whole tile was consumed.
+// Here each operand tile is kept as two halves that are consumed, and
+// refilled, one after the other:
+//
+//   A: the tile's upper half of rows (T) and lower half (B);
+//   B: columns in two halves (L and R);
+//
+// and the wave's block is four quadrants (its rows of T or B x its 32 columns
+// of L or R), taken in the order
+//   even tiles: (T,L) (T,R) (B,R) (B,L)     odd tiles: (T,R) (T,L) (B,L) (B,R)
+// with the fragments of a half (all 64 k) in registers while its quadrants
+// run.  Each quadrant's MFMAs hide the LDS reads of the half that the next
+// quadrant needs, which go to registers the current one does not read, so no
+// fragment register is doubled.  T and the tile's first column half are in
+// registers when the tile starts and the other two halves when quadrant 2
+// starts: two barriers per K tile, after which the halves just read are
+// refilled with tile kt + S.  Every load has S - 1/2 K tiles to land.
+//
+// Operand tiles go global -> LDS by buffer loads that write LDS directly, with
+// 16-byte chunks XOR-swizzled within a row so that the fragment reads
+// (ds_read_b128 of a K-contiguous operand, pairs of ds_read_b64_tr_b16 of an
+// M/N-contiguous one) are free of bank conflicts.  Every output element sums
+// its products in ascending k, 32 per MFMA, whatever the tile shape.
+//
+// RAGGED 1: M and N need not divide by the tile; 2: nor K by 128.  Every load is then
+// range-checked by a buffer resource of its own that starts at its first row
+// (rows past the end are not read; 32 scalar registers and one vector
+// instruction per load, the vector registers are all taken), chunks of a
+// K-contiguous operand at or past K are sent out of range by the lane that
+// would load them, and the epilogue stores only rows < M and columns < N.
+#pragma once
+#include "gemm_lds.h"
+
+namespace tps {
+
+namespace gq {
+
+using gl::ds_b128;
+using gl::ds_tr16;
+using gl::lds_barrier;
+using gl::lds_u32;
+using gl::pin;
+using gl::static_for;
+using gl::wait_lgkm;
+using gl::wait_vmcnt;
+
+constexpr int BK = 64;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
+}
+
+// Chunk swizzles (XOR on the 16-byte chunk index within a row):
+//  K-contiguous half, 128-byte rows: 16 lanes read 16 consecutive rows at one
+//  chunk; rows alternate between the two bank halves and (r >> 1) & 7 spreads
+//  the eight rows of each half.
+__device__ __forceinline__ int swz_kc(int r) { return (r >> 1) & 7; }
+//  M/N-contiguous half [k][W columns]: a pass of 32 lanes reads 2 chunks of 8
+//  k-rows, k0 + {0..3} and k0 + 8 + {0..3}.  W = 128 (256-byte rows): the rows'
+//  low bits pick one of 8 chunk pairs; W = 64 (128-byte rows, odd rows in the
+//  other bank half): one of 4.
+template <int W>
+__device__ __forceinline__ int swz_mc(int k) {
+  if constexpr (W == 128) return ((k & 3) << 2) | (((k >> 3) & 1) << 1);
+  else return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+}
+
+// Loads of one operand, as halves of R rows (or columns): R / 8 instructions of
+// 1 KB, dealt to the waves in turn (the swizzle of a lane is then the same for
+// all of its instructions).  Row r of half hh is row hh * R + r of the operand tile,
+// or with INTER (a K-contiguous B operand) row (r / 32) * 64 + hh * 32 + r % 32,
+// which gives a wave 64 adjacent output columns.
+template <bool KC, bool INTER, int R, int NW, int RAGGED>
+struct Loads {
+  static constexpr int INST = R / 8, IPW = INST / NW;
+  static_assert(INST % NW == 0 && (IPW == 1 || IPW == 2), "instructions per wave");
+  static constexpr int ROWB = KC ? 128 : R * 2;   // bytes per stored row
+  static constexpr int RPI = 1024 / ROWB;         // stored rows per instruction
+  // the operand tile and its bytes; RAGGED: from the first row of each of the
+  // wave's instructions (half, instruction) on
+  const char* base[RAGGED ? 2 : 1][RAGGED ? IPW : 1];
+  uint32_t bytes[RAGGED ? 2 : 1][RAGGED ? IPW : 1];
+  uint32_t voff;   // lane part
+  uint32_t ld2;    // leading dimension in bytes
+  int w;
+  // RAGGED, K-contiguous: whole K tiles, and the lanes whose chunk of the next
+  // one lies within K
+  int kfull;
+  uint64_t ktail;
+  // first row of instruction i of half hh within the operand tile (K-contiguous)
+  static __device__ __forceinline__ int row_of(int hh, int i) {
+    return INTER ? (i >> 2) * 64 + hh * 32 + (i & 3) * 8 : hh * R + i * 8;
+  }
+  __device__ __forceinline__ void init(const bf16* tile, int64_t ld, int rows, int K, int lane, int wave) {
+    const int avail = min(rows, 2 * R);
+    const char* t = reinterpret_cast<const char*>(tile);
+    const uint32_t n = (uint32_t)((KC ? (int64_t)(avail - 1) * ld + K : (int64_t)(K - 1) * ld + avail) * 2);
+    ld2 = (uint32_t)(ld * 2);
+    w = wave;
+    constexpr int CPR = ROWB / 16;
+    const int row = wave * RPI + lane / CPR;
+    static_assert(NW * RPI % 16 == 0, "rows of a wave's instructions agree modulo 16");
+    const int c = (lane % CPR) ^ (KC ? swz_kc(row) : swz_mc<KC ? 128 : R>(row));
+    voff = (uint32_t)(lane / CPR) * ld2 + (uint32_t)c * 16;
+    kfull = K / BK;
+    ktail = __builtin_amdgcn_ballot_w64(c * 8 < K % BK);
+    if constexpr (RAGGED == 0) {
+      base[0][0] = t;
+      bytes[0][0] = n;
+    } else {
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+        for (int j = 0; j < IPW; ++j) {
+          const int i = j * NW + w;
+          // a K-contiguous instruction wholly past the last row reads row 0
+          // instead (its rows are never stored)
+          int first = KC ? row_of(hh, i) : i * RPI;
+          if (KC && first >= avail) first = 0;
+          const uint32_t o = (uint32_t)first * ld2 + (KC ? 0u : (uint32_t)(hh * R * 2));
+          base[hh][j] = t + o;
+          bytes[hh][j] = (uint32_t)max((int)(n - o), 0);
+        }
+    }
+  }
+  // instruction j of this wave's share of half hh of K tile kt -> half
+  __device__ __forceinline__ void load(int j, int hh, int kt, char* half) const {
+    const int i = j * NW + w;
+    gl::lds_void* const dst = (gl::lds_void*)(half + i * 1024);
+    if constexpr (RAGGED == 0) {
+      const uint32_t o = KC ? (uint32_t)row_of(hh, i) * ld2 + (uint32_t)kt * (BK * 2)
+                            : (uint32_t)(kt * BK + i * RPI) * ld2 + (uint32_t)(hh * R * 2);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base[0][0], bytes[0][0]), dst, 16, voff, o, 0, 0);
+    } else if constexpr (KC) {
+      // rows are checked by the resource; lanes at or past K are sent out of
+      // its range (the scalar offset stays within K)
+      uint32_t v = voff;
+      if constexpr (RAGGED == 2) {
+        const uint64_t in = kt < kfull ? ~uint64_t(0) : kt == kfull ? ktail : uint64_t(0);
+        v = __builtin_amdgcn_inverse_ballot_w64(in) ? voff : 0x80000000u;
+        kt = min(kt, kfull);
+      }
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base[hh][j], bytes[hh][j]), dst, 16, v, (uint32_t)kt * (BK * 2), 0, 0);
+    } else {
+      // the whole distance is in the checked lane offset: rows at or past K read as zeros
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base[hh][j], bytes[hh][j]), dst, 16, voff + (uint32_t)(kt * BK) * ld2, 0, 0, 0);
+    }
+  }
+};
+
+// Fragments of one operand half held by a wave: NR blocks of 16 rows (columns)
+// x 2 k-steps of 32.  Lane l holds row l % 16 of a block at k = 8 (l / 16) .. +8.
+template <bool KC, int R, int NR>
+struct Frags {
+  static constexpr int NB = KC ? 2 : NR;
+  static constexpr int COUNT = 2 * NR;   // fragments per half
+  uint32_t base[NB];
+  __device__ __forceinline__ void init(uint32_t lds, int row0, int lane) {
+    if constexpr (KC) {
+      const int row = row0 + (lane & 15);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) base[ks] = lds + row * 128 + (((ks * 4 + (lane >> 4)) ^ swz_kc(row)) << 4);
+    } else {
+      const int G = lane >> 4, s = lane & 15;
+      const int k = 8 * G + (s >> 2);
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        const int col = row0 + 16 * i + ((s & 3) << 2);
+        base[i] = lds + k * (R * 2) + (((col >> 3) ^ swz_mc<R>(k)) << 4) + (col & 7) * 2;
+      }
+    }
+  }
+  // read fragment N = (k-step N / NR, block N % NR) of the half at `at` + OFF
+  template <int OFF, int N>
+  __device__ __forceinline__ void read(bf16x8 (&f)[2][NR], uint32_t at) const {
+    constexpr int ks = N / NR, i = N % NR;
+    if constexpr (KC) {
+      f[ks][i] = ds_b128<OFF + i * 2048>(base[ks] + at);
+    } else {
+      typedef __attribute__((ext_vector_type(8))) short s16x8;
+      constexpr int ROWB = R * 2;
+      const uint32_t p = base[i] + at;
+      const gl::s16x4 lo = ds_tr16<OFF + ks * 32 * ROWB>(p);
+      const gl::s16x4 hi = ds_tr16<OFF + ks * 32 * ROWB + 4 * ROWB>(p);
+      s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      f[ks][i] = *reinterpret_cast<bf16x8*>(&v);
+    }
+  }
+};
+
+// c += a b, in place.  As an instruction of its own: with the builtin the
+// register allocator moves accumulators from one tuple to another, and where
+// the tile leaves only a few registers free it spills for that.  The compiler
+// then adds no wait states for the result: an accumulator's next MFMA comes
+// several MFMAs later, and mfma_settle() precedes its first other use.
+__device__ __forceinline__ void mfma(f32x4& c, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_settle() { asm volatile("s_nop 15" ::: "memory"); }
+
+template <int NR>
+__device__ __forceinline__ void pin_all(bf16x8 (&f)[2][NR]) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int i = 0; i < NR; ++i) pin(f[k][i]);
+}
+
+}  // namespace gq
+
+template <int LAYOUT, int BM, int BN, int WGM, int WGN, int S, int EPI, int RAGGED>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * WGM * WGN, 64 * WGM * WGN), amdgpu_waves_per_eu(2, 2)))
+void gemm_quad_kernel(GemmArgs g) {
+#ifdef __HIP_DEVICE_COMPILE__   // the host pass needs the signature only (and knows no MFMA or ballot builtins)
+  using namespace gq;
+  constexpr bool A_KC = (LAYOUT != TPS_GEMM_TN), B_KC = (LAYOUT == TPS_GEMM_NT);
+  constexpr int NW = WGM * WGN, RA = BM / 2, RB = BN / 2;
+  constexpr int TA = RA / WGM / 16, TB = RB / WGN / 16;   // 16-row (column) blocks per wave and half
+  static_assert(TB == 2 && TA % 2 == 0, "epilogue strips of 32 rows, 64 columns per wave");
+  constexpr int HA = RA * BK * 2, HB = RB * BK * 2;       // bytes of a half
+  // LDS: the A halves of every stage, then the B halves
+  constexpr int LDS = 2 * S * (HA + HB), BO = 2 * S * HA;
+  static_assert(S % 2 == 0 && LDS <= 160 * 1024, "LDS ring");
+  __shared__ __attribute__((aligned(1024))) char smem[LDS];
+
+  const int nblk = g.tiles_m * g.tiles_n;
+  int pid = blockIdx.x;
+  if ((nblk & 7) == 0) pid = (pid & 7) * (nblk >> 3) + (pid >> 3);
+  constexpr int GROUP = 8;
+  const int group = pid / (GROUP * g.tiles_n);
+  const int first_m = group * GROUP;
+  const int gm = min(GROUP, g.tiles_m - first_m);
+  const int tile_m = first_m + (pid % (GROUP * g.tiles_n)) % gm;
+  const int tile_n = (pid % (GROUP * g.tiles_n)) / gm;
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+
+  const bf16* A = static_cast<const bf16*>(g.A);
+  const bf16* B = static_cast<const bf16*>(g.B);
+  typedef Loads<A_KC, false, RA, NW, RAGGED> LA;
+  typedef Loads<B_KC, B_KC, RB, NW, RAGGED> LB;
+  LA la;
+  LB lb;
+  la.init(A_KC ? A + (int64_t)m0 * g.lda : A + m0, g.lda, g.M - m0, g.K, lane, wave);
+  lb.init(B_KC ? B + (int64_t)n0 * g.ldb : B + n0, g.ldb, g.N - n0, g.K, lane, wave);
+  constexpr int LPG = LA::IPW + LB::IPW;   // loads per wave and group
+
+  // group 1 of tile kt: T and the first column half (half kt % 2); group 2: the rest
+  auto load1 = [&](auto pc, auto nc, int kt, int st) {
+    constexpr int P = decltype(pc)::value, n = decltype(nc)::value;
+    if constexpr (n < LA::IPW) la.load(n, 0, kt, smem + st * 2 * HA);
+    else lb.load(n - LA::IPW, P, kt, smem + BO + (st * 2 + P) * HB);
+  };
+  auto load2 = [&](auto pc, auto nc, int kt, int st) {
+    constexpr int P = decltype(pc)::value, n = decltype(nc)::value;
+    if constexpr (n < LB::IPW) lb.load(n, P ^ 1, kt, smem + BO + (st * 2 + (P ^ 1)) * HB);
+    else la.load(n - LB::IPW, 1, kt, smem + (st * 2 + 1) * HA);
+  };
+
+  f32x4 acc[2 * TA][2 * TB];   // [T blocks, B blocks][L blocks, R blocks]
+#pragma unroll
+  for (int i = 0; i < 2 * TA; ++i)
+#pragma unroll
+    for (int j = 0; j < 2 * TB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  Frags<A_KC, RA, TA> fra;
+  Frags<B_KC, RB, TB> frb;
+  fra.init(lds_u32(smem), wm * 16 * TA, lane);
+  frb.init(lds_u32(smem) + BO, wn * 16 * TB, lane);
+  bf16x8 fa[2][2][TA];   // T, B
+  bf16x8 fb[2][2][TB];   // L, R
+
+  // an even number of K tiles, at least S (the loop takes them in pairs, which
+  // keeps its control flow, and with it the accumulators, straight); RAGGED:
+  // those past K read as zeros
+  const int nk = max(S, (g.K + 2 * BK - 1) / (2 * BK) * 2);
+  using P0 = std::integral_constant<int, 0>;
+  using P1 = std::integral_constant<int, 1>;
+
+  static_for<S>([&](auto tc) {
+    constexpr int t = decltype(tc)::value;
+    using P = std::integral_constant<int, t % 2>;
+    static_for<LPG>([&](auto n) { load1(P{}, n, t, t); });
+    static_for<LPG>([&](auto n) { load2(P{}, n, t, t); });
+  });
+  wait_vmcnt<(2 * S - 1) * LPG>();   // group 1 of tile 0 landed
+  lds_barrier();
+  static_for<2 * TA>([&](auto n) { fra.template read<0, decltype(n)::value>(fa[0], 0); });
+  static_for<2 * TB>([&](auto n) { frb.template read<0, decltype(n)::value>(fb[0], 0); });
+
+  // One K tile of parity P in stage st.  AHEAD: K tiles after this one whose
+  // loads have been issued; REFILL: tile kt + S exists (loaded as this tile's
+  // halves are read; AHEAD is then S - 1).
+  auto k_tile = [&](auto pc, int kt, int st, auto ahead_c, auto refill_c) {
+    constexpr int P = decltype(pc)::value, AHEAD = decltype(ahead_c)::value;
+    constexpr bool REFILL = decltype(refill_c)::value, NEXT = AHEAD > 0;
+    constexpr int F = P, X = P ^ 1;   // first and second column half
+    // LDS offsets of this tile's stage and the next one's: immediates where the
+    // stage is the parity, else added to the fragment addresses
+    constexpr int CA = S == 2 ? P * 2 * HA : 0, CB = S == 2 ? P * 2 * HB : 0;
+    constexpr int NA = S == 2 ? X * 2 * HA : 0, NB = S == 2 ? X * 2 * HB : 0;
+    const int sn = st + 1 == S ? 0 : st + 1;
+    const uint32_t ca = S == 2 ? 0 : (uint32_t)(st * 2 * HA), cb = S == 2 ? 0 : (uint32_t)(st * 2 * HB);
+    const uint32_t na = S == 2 ? 0 : (uint32_t)(sn * 2 * HA), nb = S == 2 ? 0 : (uint32_t)(sn * 2 * HB);
+    // quadrant (A half ah, column half bh); mid(m) after MFMA m
+    constexpr int NM = 2 * TA * TB;
+    auto quad = [&](auto ahc, auto bhc, auto&& mid) {
+      constexpr int ah = decltype(ahc)::value, bh = decltype(bhc)::value;
+      static_for<NM>([&](auto mc) {
+        constexpr int m = decltype(mc)::value, ks = m / (TA * TB), i = (m / TB) % TA, j = m % TB;
+        // operands swapped: a lane holds 4 adjacent columns of one row
+        mfma(acc[ah * TA + i][bh * TB + j], fb[bh][ks][j], fa[ah][ks][i]);
+        mid(mc);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    using FH = std::integral_constant<int, F>;
+    using XH = std::integral_constant<int, X>;
+    constexpr int RH = NM / 2;   // loads go after the LDS reads, in the second half of a quadrant
+    // ---- quadrant 0 (T, first): T and the first half of this tile are in
+    // registers on every wave after the barrier, and its other halves in LDS
+    wait_lgkm<0>();
+    pin_all(fa[0]);
+    pin_all(fb[F]);
+    wait_vmcnt<2 * AHEAD * LPG>();
+    lds_barrier();
+    quad(P0{}, FH{}, [&](auto mc) {
+      constexpr int m = decltype(mc)::value;
+      if constexpr (m < 2 * TB) frb.template read<CB + X * HB, m>(fb[X], cb);
+      if constexpr (REFILL && m >= RH && m < RH + LPG) load1(pc, std::integral_constant<int, m - RH>{}, kt + S, st);
+    });
+    // ---- quadrant 1 (T, second)
+    wait_lgkm<0>();
+    pin_all(fb[X]);
+    quad(P0{}, XH{}, [&](auto mc) {
+      constexpr int m = decltype(mc)::value;
+      if constexpr (m < 2 * TA) fra.template read<CA + HA, m>(fa[1], ca);
+    });
+    // ---- quadrant 2 (B, second): every half of this tile is in registers
+    // after the barrier, and group 1 of the next tile in LDS
+    wait_lgkm<0>();
+    pin_all(fa[1]);
+    if constexpr (NEXT) {
+      wait_vmcnt<(2 * AHEAD - (REFILL ? 0 : 1)) * LPG>();
+      lds_barrier();
+    }
+    quad(P1{}, XH{}, [&](auto mc) {
+      constexpr int m = decltype(mc)::value;
+      if constexpr (NEXT && m < 2 * TA) fra.template read<NA, m>(fa[0], na);
+      if constexpr (REFILL && m >= RH && m < RH + LPG) load2(pc, std::integral_constant<int, m - RH>{}, kt + S, st);
+    });
+    // ---- quadrant 3 (B, first): the second half's registers take the next
+    // tile's first column half (which is this tile's second)
+    quad(P1{}, FH{}, [&](auto mc) {
+      constexpr int m = decltype(mc)::value;
+      if constexpr (NEXT && m < 2 * TB) frb.template read<NB + X * HB, m>(fb[X], nb);
+    });
+  };
+  using Full = std::integral_constant<int, S - 1>;
+  int kt = 0, st = 0;
+  for (; kt + S < nk; kt += 2) {
+    k_tile(P0{}, kt, st, Full{}, std::true_type{});
+    k_tile(P1{}, kt + 1, st + 1, Full{}, std::true_type{});
+    st = st + 2 == S ? 0 : st + 2;
+  }
+  static_for<S>([&](auto tc) {
+    constexpr int t = decltype(tc)::value;
+    k_tile(std::integral_constant<int, t % 2>{}, kt + t, (st + t) % S, std::integral_constant<int, S - 1 - t>{},
+           std::false_type{});
+  });
+  mfma_settle();
+#pragma unroll
+  for (int i = 0; i < 2 * TA; ++i)
+#pragma unroll
+    for (int j = 0; j < 2 * TB; ++j) pin(acc[i][j]);
+  __syncthreads();   // LDS is reused below
+
+  auto row_of = [&](int i) { return m0 + (i / (TA / 2)) * RA + wm * 16 * TA + (i % (TA / 2)) * 32; };
+  auto col_of = [&](int c) { return B_KC ? n0 + wn * 64 + c : n0 + (c >> 5) * RB + wn * 32 + (c & 31); };
+  gemm_epilogue<EPI, RAGGED != 0, NW, TA, LDS>(g, acc, smem, row_of, col_of, lane, wave);
+#endif
+}
+
+template <int LAYOUT, int BM, int BN, int WGM, int WGN, int S, int EPI>
+static hipError_t launch_quad(GemmArgs g, hipStream_t stream) {
+  g.tiles_m = (g.M + BM - 1) / BM;
+  g.tiles_n = (g.N + BN - 1) / BN;
+  const dim3 grid(g.tiles_m * g.tiles_n), block(64 * WGM * WGN);
+  if (g.K % 128 != 0)
+    hipLaunchKernelGGL((gemm_quad_kernel<LAYOUT, BM, BN, WGM, WGN, S, EPI, 2>), grid, block, 0, stream, g);
+  else if (g.M % BM != 0 || g.N % BN != 0)
+    hipLaunchKernelGGL((gemm_quad_kernel<LAYOUT, BM, BN, WGM, WGN, S, EPI, 1>), grid, block, 0, stream, g);
+  else
+    hipLaunchKernelGGL((gemm_quad_kernel<LAYOUT, BM, BN, WGM, WGN, S, EPI, 0>), grid, block, 0, stream, g);
+  return hipGetLastError();
+}
+
+}  // namespace tps

@@ -1,6 +1,7 @@
 // Op-level C ABI (tpstage_ops.h): argument checks, then one kernel launch
 // sequence on the caller's stream.
 #include <cstdio>
+#include <mutex>
 #include <string>
 
 #include "errors.h"
@@ -217,7 +218,7 @@ extern "C" uint64_t tps_op_workspace_bytes(int kind, int64_t rows, int64_t cols)
 
 namespace tps {
 
-static bool v2_epilogue(int layout, int epi) {
+static bool fast_epilogue(int layout, int epi) {
   if (layout == TPS_GEMM_NT)
     return epi == TPS_EPI_STORE || epi == TPS_EPI_BIAS || epi == TPS_EPI_BIAS_RESID || epi == TPS_EPI_BIAS_GELU ||
            epi == TPS_EPI_GELU_GRAD;
@@ -229,51 +230,53 @@ static bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) 
 
 GemmTile gemm_select_tile(int dtype, int layout, const GemmArgs& g) {
   const int M = g.M, N = g.N, K = g.K;
-  if (dtype == TPS_BF16) {
-    // tile-aligned path: every operand 16-byte aligned with leading dimensions
-    // in whole 16-byte chunks, and an epilogue it instantiates
-    bool ok = K % 64 == 0 && K > 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && v2_epilogue(layout, g.epi) &&
-              al16(g.A) && al16(g.B) && al16(g.C) && g.ldc % 8 == 0;
-    if (g.epi == TPS_EPI_BIAS || g.epi == TPS_EPI_BIAS_RESID || g.epi == TPS_EPI_BIAS_GELU) ok = ok && al16(g.bias);
-    if (g.epi == TPS_EPI_BIAS_RESID) ok = ok && al16(g.resid) && g.ldr % 8 == 0;
-    if (g.epi == TPS_EPI_BIAS_GELU || g.epi == TPS_EPI_GELU_GRAD) ok = ok && al16(g.aux) && g.ldaux % 8 == 0;
-    if (ok && M % 256 == 0 && N % 256 == 0 && (int64_t)(M / 256) * (N / 256) >= 160) return {256, 256, 32, 1};
-    if (ok && M % 128 == 0 && N % 128 == 0) return {128, 128, 32, 1};
-    const int64_t t256 = (int64_t)((M + 255) / 256) * ((N + 127) / 128);
-    if (t256 >= 256) return {256, 128, 64, 0};
-    return {128, 128, 64, 0};
+  if (dtype != TPS_BF16) return {128, 128, 32, 0};
+  // direct-to-LDS kernels: every operand 16-byte aligned with leading
+  // dimensions in whole 16-byte chunks, an epilogue they instantiate, and
+  // tile offsets within the 32 bits of a buffer load (2 GiB leaves room for
+  // the offset that sends a chunk out of range)
+  bool ok = K > 0 && N % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && fast_epilogue(layout, g.epi) && al16(g.A) &&
+            al16(g.B) && al16(g.C) && g.ldc % 8 == 0;
+  if (g.epi == TPS_EPI_BIAS || g.epi == TPS_EPI_BIAS_RESID || g.epi == TPS_EPI_BIAS_GELU) ok = ok && al16(g.bias);
+  if (g.epi == TPS_EPI_BIAS_RESID) ok = ok && al16(g.resid) && g.ldr % 8 == 0;
+  if (g.epi == TPS_EPI_BIAS_GELU || g.epi == TPS_EPI_GELU_GRAD) ok = ok && al16(g.aux) && g.ldaux % 8 == 0;
+  const int64_t lim = int64_t(1) << 31;
+  const int64_t ra = layout == TPS_GEMM_TN ? K : 256, rb = layout == TPS_GEMM_NT ? 256 : K;
+  ok = ok && (ra + 128) * g.lda * 2 + 512 < lim && (rb + 128) * g.ldb * 2 + 512 < lim;
+  if (ok) {
+    // 128 x 128 tiles run two workgroups per CU, 256 x 256 tiles one.  While
+    // the small tiles fit the chip at once (512) they win, 1.25-2x below half
+    // of that; past it the large ones are 5-12% faster (up to 30% for long
+    // NN contractions), unless padding M and N to them costs more than that
+    // (2048 x 4096 x 2048, 512 small tiles: 32 against 40 us; 3000 x 3072 x
+    // 3072, 576: 61 against 58 us; 4096 x 4096 x 4096, 1024: 113 against 100 us).
+    const int64_t t256 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
+    const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
+    return t128 > 512 && t256 * 28 <= t128 * 8 ? GemmTile{256, 256, 64, 1} : GemmTile{128, 128, 64, 1};
   }
-  return {128, 128, 32, 0};
+  const int64_t t = (int64_t)((M + 255) / 256) * ((N + 127) / 128);
+  return t >= 256 ? GemmTile{256, 128, 64, 0} : GemmTile{128, 128, 64, 0};
 }
 
 const char* gemm_kernel_name(int dtype, int layout, const GemmArgs& g) {
-  static const char* v1[2][2][3] = {
-      {{"tps::gemm_kernel<float, 128, 128, 32, 0>", "tps::gemm_kernel<float, 128, 128, 32, 1>",
-        "tps::gemm_kernel<float, 128, 128, 32, 2>"},
-       {"tps::gemm_kernel<float, 128, 128, 32, 0>", "tps::gemm_kernel<float, 128, 128, 32, 1>",
-        "tps::gemm_kernel<float, 128, 128, 32, 2>"}},
-      {{"tps::gemm_kernel<__bf16, 128, 128, 64, 0>", "tps::gemm_kernel<__bf16, 128, 128, 64, 1>",
-        "tps::gemm_kernel<__bf16, 128, 128, 64, 2>"},
-       {"tps::gemm_kernel<__bf16, 256, 128, 64, 0>", "tps::gemm_kernel<__bf16, 256, 128, 64, 1>",
-        "tps::gemm_kernel<__bf16, 256, 128, 64, 2>"}}};
-  // [long K][tile][layout][epilogue]
-  static char v3[2][2][3][6][64];
-  static bool init = false;
-  if (!init) {
-    for (int k = 0; k < 2; ++k)
-      for (int t = 0; t < 2; ++t)
-        for (int l = 0; l < 3; ++l)
+  // [dtype][tile][layout] of the generic kernel, [ragged][tile][layout][epilogue] of the others
+  static char gen[2][2][3][64], fast[3][2][3][6][80];
+  static std::once_flag once;
+  std::call_once(once, [] {
+    for (int l = 0; l < 3; ++l)
+      for (int t = 0; t < 2; ++t) {
+        snprintf(gen[0][t][l], sizeof(gen[0][t][l]), "tps::gemm_kernel<float, 128, 128, 32, %d>", l);
+        snprintf(gen[1][t][l], sizeof(gen[1][t][l]), "tps::gemm_kernel<__bf16, %d, 128, 64, %d>", t ? 256 : 128, l);
+        for (int r = 0; r < 3; ++r)
           for (int e = 0; e < 6; ++e) {
-            const V3Config c = v3_config(l, t == 1, k == 1);
-            const int tile = t ? 256 : 128;
-            snprintf(v3[k][t][l][e], sizeof(v3[k][t][l][e]), "tps::gemm_bf16_kernel<%d, %d, %d, %d, %d, %d, %d, %d>",
-                     l, tile, tile, c.wgm, c.wgn, c.bk, c.stages, e);
+            snprintf(fast[r][t][l][e], sizeof(fast[r][t][l][e]), "tps::gemm_quad_kernel<%d, %d, %d, 2, %d, %d, %d, %d>", l,
+                     t ? 256 : 128, t ? 256 : 128, t ? 4 : 2, 2, e, r);
           }
-    init = true;
-  }
+      }
+  });
   const GemmTile t = gemm_select_tile(dtype, layout, g);
-  if (t.aligned) return v3[g.K >= TN_LONG_K][t.bm == 256][layout][g.epi];
-  return v1[dtype == TPS_BF16][t.bm == 256][layout];
+  if (t.fast) return fast[g.K % 128 ? 2 : g.M % t.bm || g.N % t.bn ? 1 : 0][t.bm == 256][layout][g.epi];
+  return gen[dtype == TPS_BF16][t.bm == 256][layout];
 }
 
 hipError_t gemm_launch(int dtype, int layout, int epi, int M, int N, int K, const void* A, int64_t lda,

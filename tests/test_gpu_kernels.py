@@ -26,11 +26,9 @@ def _round(a, dtype):
     return synth.round_to_storage(np.asarray(a, dtype=np.float32), dtype).astype(np.float64)
 
 
-# ragged shapes take the generic path; tile-aligned ones (M, N multiples of
-# 128 or 256, K of 64) take the direct-to-LDS path at both tile sizes: 256 x
-# 256 tiles (2-stage ring) at 1 and 2 K tiles, 128 x 128 tiles (4-stage ring,
-# fragments read two k-steps ahead) at 1, 2, 3, 4, 5 and 8 K tiles, so the
-# ring's fill, refill and drain each meet short and long loops
+# aligned and ragged shapes at both tile sizes of the direct-to-LDS kernel (128 x
+# 128 up to 512 tiles, 256 x 256 past that), with 1, 2, 3, 4 and more K tiles
+# of 64 (the loop takes them in pairs); f32 takes the generic kernel
 GEMM_SHAPES = [(200, 264, 136), (1000, 520, 72), (64, 64, 8), (2072, 4104, 264),
                (256, 384, 192), (4096, 2560, 128), (384, 256, 512), (128, 128, 64), (256, 128, 128),
                (128, 256, 256), (384, 128, 320), (4096, 2560, 64)]
@@ -54,6 +52,36 @@ def test_gemm_store(dtype, layout, shape):
     T.op_gemm(DT[dtype], layout, T.EPI_STORE, M, N, K, dA, a_shape[1], dB, b_shape[1], dC, N)
     torch.cuda.synchronize()
     assert_close(to_np(dC), ref, TOL[dtype])
+
+
+@pytest.mark.parametrize("layout", [T.GEMM_NT, T.GEMM_NN, T.GEMM_TN])
+@pytest.mark.parametrize("shape", [
+    (8, 8, 8), (136, 120, 64), (120, 136, 1000), (264, 392, 384),      # 128 x 128 tiles
+    (2056, 8328, 72), (4104, 4232, 256), (5888, 3080, 520)])           # 256 x 256 tiles
+def test_gemm_ragged_edges(layout, shape):
+    """M, N and K that leave part of a tile: nothing outside the operands may
+    reach the result (their padding columns hold NaN, and TN's last rows end
+    the allocation) and nothing outside C may be written."""
+    import torch
+    M, N, K = shape
+    K -= 3 if layout == T.GEMM_TN else 0   # TN: any number of rows
+    a_shape = (K, M) if layout == T.GEMM_TN else (M, K)
+    b_shape = (N, K) if layout == T.GEMM_NT else (K, N)
+    A, B = _t(51, a_shape, "bf16"), _t(52, b_shape, "bf16")
+    pad = 8
+
+    def padded(v):
+        t = torch.full((v.shape[0], v.shape[1] + pad), float("nan"), dtype=torch.bfloat16, device="cuda")
+        t[:, :v.shape[1]] = to_dev(v, "bf16")
+        return t
+    dA, dB = padded(A), padded(B)
+    dC = torch.full((M, N + pad), 7.0, dtype=torch.bfloat16, device="cuda")
+    T.op_gemm(T.TPS_BF16, layout, T.EPI_STORE, M, N, K, dA, a_shape[1] + pad, dB, b_shape[1] + pad, dC, N + pad)
+    torch.cuda.synchronize()
+    Am = torch.from_numpy(A).cuda().T if layout == T.GEMM_TN else torch.from_numpy(A).cuda()
+    Bm = torch.from_numpy(B).cuda().T if layout == T.GEMM_NT else torch.from_numpy(B).cuda()
+    assert_close(to_np(dC[:, :N]), (Am.double() @ Bm.double()).cpu().numpy(), TOL["bf16"])
+    assert bool((dC[:, N:] == 7.0).all())
 
 
 @pytest.mark.parametrize("dtype,shape", [("f32", (296, 392, 200)), ("bf16", (296, 392, 200)),
