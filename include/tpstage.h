@@ -238,7 +238,9 @@ typedef struct tps_memory {
                                    segment replays) onto streams of its own
                                    and joins them back before anything on this
                                    stream reads their results, and at the end
-                                   of each forward and of the iteration       */
+                                   of each forward and of the iteration.  Those
+                                   streams are shared by the stages that
+                                   compute on the same stream                 */
   void* copy_stream;            /* hipStream_t for device -> host copies, or
                                    NULL: the stage creates its own             */
   void* prefetch_stream;        /* hipStream_t for host -> device copies, or
@@ -374,6 +376,16 @@ int tps_stage_kernel_times(tps_stage* st, tps_kernel_time* out, int max, int* n_
 
 /* Releases events and host metadata (caller buffers are untouched). */
 int tps_stage_destroy(tps_stage* st);
+
+/* A compute stream for stages whose caller works on the null stream: one per
+ * device (the current one), shared by everything that acquires it, on a
+ * hardware queue of its own.  It synchronizes with the null stream both ways,
+ * so a caller on the null stream needs no events around the stage's calls.
+ * Every acquire is followed by one release, after the stages using the stream
+ * are destroyed; the last release destroys it.  TPS_EINVAL for a stream that is
+ * not acquired. */
+int tps_compute_stream_acquire(void** out);
+int tps_compute_stream_release(void* stream);
 
 /* Pinned (page-locked) host memory of exactly `bytes` bytes, for the host
  * side of streamed weights and gradients and for the host arena: T-Offload

@@ -134,6 +134,7 @@ EXPORTED = (
     "tps_op_attention_bwd_noalloc_max_rows", "tps_param_layout_q", "tps_host_adamw_layer",
     "tps_stage_set_optimizer", "tps_stage_set_optimizer_split", "tps_op_dequant_fp8_rows", "tps_op_rmsnorm_fwd",
     "tps_op_rmsnorm_bwd", "tps_op_rope",
+    "tps_compute_stream_acquire", "tps_compute_stream_release",
     "tps_op_swiglu_fwd", "tps_op_swiglu_bwd", "tps_op_attention_gqa_fwd", "tps_op_attention_gqa_bwd",
 )
 
@@ -188,6 +189,8 @@ def lib() -> C.CDLL:
         L.tps_op_workspace_bytes.restype = u64
         L.tps_host_alloc.argtypes = [u64, C.POINTER(vp)]
         L.tps_host_free.argtypes = [vp]
+        L.tps_compute_stream_acquire.argtypes = [C.POINTER(vp)]
+        L.tps_compute_stream_release.argtypes = [vp]
         L.tps_param_layout_q.argtypes = [C.POINTER(Config), C.POINTER(C.c_uint64), C.POINTER(C.c_uint64),
                                          C.POINTER(C.c_uint64)]
         L.tps_host_adamw_layer.argtypes = [C.POINTER(Config), C.POINTER(AdamW), i32, vp, vp, vp, vp, vp, i32, i32]
@@ -453,12 +456,14 @@ class Stage:
 
     Stream order: the stage's kernels run on its compute stream `cs`: the
     given one, else the stream current at construction unless that is the
-    device's default (null) stream, else a private stream.  Every call that
-    enqueues work first makes `cs` wait for the caller's current stream (so
-    inputs and parameters written there are complete) and afterwards makes
-    the caller's current stream wait for `cs` (so outputs are complete, and
-    buffers freed there are not reused while the stage still reads them).
-    When the two are the same stream no event is needed.  Work on the
+    device's default (null) stream, else a stream of the library's that the
+    stages of the device share and that synchronizes with the default stream
+    both ways.  Every call that enqueues work first makes `cs` wait for the
+    caller's current stream (so inputs and parameters written there are
+    complete) and afterwards makes the caller's current stream wait for `cs`
+    (so outputs are complete, and buffers freed there are not reused while the
+    stage still reads them).  When the two are the same stream, or the shared
+    stream and the default stream, no event is needed.  Work on the
     default stream synchronizes with the copy and side streams the library
     creates, so callers that want calls to overlap the library's copies run
     under a `torch.cuda.stream(...)` of their own."""
@@ -472,10 +477,19 @@ class Stage:
         self.arena = torch.empty(max(self.info["device_arena_bytes"], 256), dtype=torch.uint8, device=self.device)
         hb = self.info["host_arena_bytes"]
         self.host = HostBuffer(hb) if hb else None
-        # compute on a torch stream; copy streams default to the stage's own
+        # compute on a torch stream or the shared one; copy streams default to
+        # the stage's own
+        self._shared_cs = None
         if compute_stream is None:
             cur = torch.cuda.current_stream(self.device)
-            compute_stream = cur if cur.cuda_stream != 0 else torch.cuda.Stream(device=self.device)
+            if cur.cuda_stream != 0:
+                compute_stream = cur
+            else:
+                p = C.c_void_p()
+                with torch.cuda.device(self.device):
+                    check(lib().tps_compute_stream_acquire(C.byref(p)))
+                self._shared_cs = p.value
+                compute_stream = torch.cuda.ExternalStream(p.value, device=self.device)
         self.cs = compute_stream
         self.xs, self.ps = copy_stream, prefetch_stream
         self.layer_params, self.layer_grads = list(layer_params), list(layer_grads)
@@ -496,7 +510,7 @@ class Stage:
         the class docstring."""
         import torch
         cur = torch.cuda.current_stream(self.device)
-        same = cur.cuda_stream == self.cs.cuda_stream
+        same = cur.cuda_stream == self.cs.cuda_stream or (self._shared_cs is not None and cur.cuda_stream == 0)
         if not same:
             self.cs.wait_stream(cur)
         try:
@@ -579,6 +593,9 @@ class Stage:
         if getattr(self, "handle", None):
             lib().tps_stage_destroy(self.handle)
             self.handle = None
+        if getattr(self, "_shared_cs", None):
+            lib().tps_compute_stream_release(self._shared_cs)
+            self._shared_cs = None
 
     def __del__(self):
         try:

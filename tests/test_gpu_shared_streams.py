@@ -1,0 +1,95 @@
+"""Streams that the stages of a device share: the compute stream of callers on
+the default stream, and the side streams of the stages on one compute stream."""
+import ctypes as C
+import threading
+
+import pytest
+
+from paper_2503_03182_amd import configs as W
+from paper_2503_03182_amd import tpstage as T
+
+from stage_harness import bit_equal, drive_iteration, inputs, make_params, read_grads, run_gpu, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(**kw):
+    return T.StageConfig(n_layers=3, hidden=256, n_heads=4, mlp=512, seq=72, micro_batch=2, n_micro=3, dtype="bf16",
+                         policy=W.policy_selective(3), **kw)
+
+
+def _buffers(cfg):
+    import torch
+    xs, dys = inputs(cfg)
+    X, DY = [to_dev(x, cfg.dtype) for x in xs], [to_dev(d, cfg.dtype) for d in dys]
+    return X, DY, [torch.empty_like(x) for x in X], [torch.empty_like(x) for x in X]
+
+
+def test_default_stream_event_covers_the_stage():
+    """A caller on the default stream hands the outputs to a stream of its own
+    with one event, while the GPU is still behind a spin kernel."""
+    import torch
+    cfg = _cfg()
+    ref = run_gpu(cfg)
+    blocks, grads, _ = make_params(cfg)
+    X, DY, Y, DX = _buffers(cfg)
+    st = T.Stage(cfg, blocks, grads)
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    torch.cuda._sleep(50_000_000)
+    drive_iteration(st, cfg, X, DY, Y, DX)
+    ev = torch.cuda.Event()
+    ev.record()
+    with torch.cuda.stream(other):
+        other.wait_event(ev)
+        got = [t.clone() for t in Y + DX]
+    other.synchronize()
+    assert bit_equal(dict(ys=ref["ys"], dxs=ref["dxs"], grads=[]),
+                     dict(ys=[to_np(t) for t in got[:3]], dxs=[to_np(t) for t in got[3:]], grads=[])) == []
+    st.close()
+
+
+@pytest.mark.parametrize("own_stream", [False, True])
+def test_two_stages_in_two_threads(own_stream):
+    """Two stages driven at once from two threads, on the shared compute stream
+    (default-stream callers) and on streams of their own."""
+    import torch
+    cfg = _cfg()
+    ref = run_gpu(cfg)
+    out, err = [None, None], []
+
+    def work(i):
+        try:
+            torch.cuda.set_device(0)
+            with torch.cuda.stream(torch.cuda.Stream() if own_stream else torch.cuda.default_stream()):
+                blocks, grads, _ = make_params(cfg)
+                X, DY, Y, DX = _buffers(cfg)
+                st = T.Stage(cfg, blocks, grads)
+                for _ in range(4):
+                    drive_iteration(st, cfg, X, DY, Y, DX)
+                st.sync()
+                torch.cuda.current_stream().synchronize()
+                out[i] = dict(ys=[to_np(y) for y in Y], dxs=[to_np(d) for d in DX], grads=read_grads(cfg, grads))
+                st.close()
+        except Exception as e:   # reported by the main thread
+            err.append(e)
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not err, err
+    for o in out:
+        assert bit_equal(ref, o) == []
+
+
+def test_compute_stream_is_shared_and_given_back():
+    import torch
+    a, b = C.c_void_p(), C.c_void_p()
+    torch.cuda.synchronize()
+    T.check(T.lib().tps_compute_stream_acquire(C.byref(a)))
+    T.check(T.lib().tps_compute_stream_acquire(C.byref(b)))
+    assert a.value and a.value == b.value
+    T.check(T.lib().tps_compute_stream_release(a))
+    T.check(T.lib().tps_compute_stream_release(b))
+    assert T.lib().tps_compute_stream_release(b) == T.TPS_EINVAL
