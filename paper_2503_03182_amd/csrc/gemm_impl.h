@@ -8,7 +8,7 @@
 //                                  accumulated into f32 (+=)
 //
 // bf16 products whose operands are 16-byte aligned take the direct-to-LDS
-// kernel of gemm_quad.h.  The kernel here serves f32 and everything else: both
+// kernel of gemm_quad.h, small f32 ones that of gemm_f32.h.  The kernel here serves everything else: both
 // operands are staged in LDS K-contiguous ([rows][BK + pad]) so that every lane
 // reads its MFMA fragment with one 16-byte LDS read, and operands that are
 // contiguous along M or N in memory are transposed on the way in: each thread
@@ -17,6 +17,7 @@
 // K), the alignment and the data.
 #pragma once
 #include <type_traits>
+#include "gemm_f32.h"
 #include "gemm_quad.h"
 #include "kernels.h"
 #include "tps_device.h"
@@ -280,6 +281,7 @@ static hipError_t launch_layout(int dtype, GemmArgs g, hipStream_t stream) {
     if (t.bm == 256) return launch_tile<bf16, 256, 128, 64, LAYOUT>(g, stream);
     return launch_tile<bf16, 128, 128, 64, LAYOUT>(g, stream);
   }
+  if (t.bm == 32) return launch_f32<LAYOUT>(g, stream);
   return launch_tile<float, 128, 128, 32, LAYOUT>(g, stream);
 }
 

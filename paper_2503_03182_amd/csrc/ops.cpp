@@ -230,7 +230,13 @@ static bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) 
 
 GemmTile gemm_select_tile(int dtype, int layout, const GemmArgs& g) {
   const int M = g.M, N = g.N, K = g.K;
-  if (dtype != TPS_BF16) return {128, 128, 32, 0};
+  if (dtype != TPS_BF16) {
+    // up to half the chip in 128 x 128 tiles: 32 x 32 blocks (gemm_f32.h has the
+    // times on both sides)
+    const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
+    if (t128 <= 128) return {32, 32, 32, 0};
+    return {128, 128, 32, 0};
+  }
   // direct-to-LDS kernels: every operand 16-byte aligned with leading
   // dimensions in whole 16-byte chunks, an epilogue they instantiate, and
   // tile offsets within the 32 bits of a buffer load (2 GiB leaves room for
@@ -259,13 +265,13 @@ GemmTile gemm_select_tile(int dtype, int layout, const GemmArgs& g) {
 }
 
 const char* gemm_kernel_name(int dtype, int layout, const GemmArgs& g) {
-  // [dtype][tile][layout] of the generic kernel, [ragged][tile][layout][epilogue] of the others
+  // [dtype][tile][layout] of the generic and the small f32 kernel, [ragged][tile][layout][epilogue] of the others
   static char gen[2][2][3][64], fast[3][2][3][6][80];
   static std::once_flag once;
   std::call_once(once, [] {
     for (int l = 0; l < 3; ++l)
       for (int t = 0; t < 2; ++t) {
-        snprintf(gen[0][t][l], sizeof(gen[0][t][l]), "tps::gemm_kernel<float, 128, 128, 32, %d>", l);
+        snprintf(gen[0][t][l], sizeof(gen[0][t][l]), t ? "tps::gemm_kernel<float, 128, 128, 32, %d>" : "tps::gemm_f32_kernel<%d>", l);
         snprintf(gen[1][t][l], sizeof(gen[1][t][l]), "tps::gemm_kernel<__bf16, %d, 128, 64, %d>", t ? 256 : 128, l);
         for (int r = 0; r < 3; ++r)
           for (int e = 0; e < 6; ++e) {
@@ -276,7 +282,7 @@ const char* gemm_kernel_name(int dtype, int layout, const GemmArgs& g) {
   });
   const GemmTile t = gemm_select_tile(dtype, layout, g);
   if (t.fast) return fast[g.K % 128 ? 2 : g.M % t.bm || g.N % t.bn ? 1 : 0][t.bm == 256][layout][g.epi];
-  return gen[dtype == TPS_BF16][t.bm == 256][layout];
+  return gen[dtype == TPS_BF16][t.bm == (dtype == TPS_BF16 ? 256 : 128)][layout];
 }
 
 hipError_t gemm_launch(int dtype, int layout, int epi, int M, int N, int K, const void* A, int64_t lda,

@@ -84,6 +84,31 @@ def test_gemm_ragged_edges(layout, shape):
     assert bool((dC[:, N:] == 7.0).all())
 
 
+@pytest.mark.parametrize("layout", [T.GEMM_NT, T.GEMM_NN, T.GEMM_TN])
+@pytest.mark.parametrize("shape", [(4, 4, 4), (36, 68, 36), (100, 260, 260), (1000, 512, 516)])
+def test_gemm_f32_small_edges(layout, shape):
+    """The 32 x 32-block f32 kernel: remainders of the block, of a wave's 32 k and
+    of the 256 k of the eight waves, with NaN around the operands."""
+    import torch
+    M, N, K = shape
+    K -= 3 if layout == T.GEMM_TN else 0
+    a_shape = (K, M) if layout == T.GEMM_TN else (M, K)
+    b_shape = (N, K) if layout == T.GEMM_NT else (K, N)
+    A, B = _t(53, a_shape, "f32"), _t(54, b_shape, "f32")
+
+    def padded(v):
+        t = torch.full((v.shape[0], v.shape[1] + 4), float("nan"), device="cuda")
+        t[:, :v.shape[1]] = torch.from_numpy(v).cuda()
+        return t
+    dC = torch.full((M, N + 4), 7.0, device="cuda")
+    T.op_gemm(T.TPS_F32, layout, T.EPI_STORE, M, N, K, padded(A), a_shape[1] + 4, padded(B), b_shape[1] + 4, dC, N + 4)
+    torch.cuda.synchronize()
+    Am = A.astype(np.float64).T if layout == T.GEMM_TN else A.astype(np.float64)
+    Bm = B.astype(np.float64).T if layout == T.GEMM_NT else B.astype(np.float64)
+    assert_close(to_np(dC[:, :N]), Am @ Bm, TOL["f32"])
+    assert bool((dC[:, N:] == 7.0).all())
+
+
 @pytest.mark.parametrize("dtype,shape", [("f32", (296, 392, 200)), ("bf16", (296, 392, 200)),
                                          ("bf16", (512, 768, 256)), ("bf16", (4096, 2560, 128))])
 def test_gemm_epilogues(dtype, shape):
