@@ -558,7 +558,7 @@ hipError_t attention_fwd_launch(int dtype, int b, int s, int nh, int nkv, int d,
   if (nkv != nh && !(dtype == TPS_BF16 && d == 128)) return hipErrorInvalidValue;
   if (dtype == TPS_BF16) {
     if (d == 128) return attention_fwd_v3_launch(b, s, nh, nkv, d, qkv, o, lse, st);
-    return attention_fwd_v2_launch(b, s, nh, d, qkv, o, lse, st);
+    return attention_fwd16_launch(b, s, nh, nkv, d, qkv, o, lse, st);
   }
   return d == 64 ? fwd_launch<float, 64>(b, s, nh, qkv, o, lse, st) : fwd_launch<float, 128>(b, s, nh, qkv, o, lse, st);
 }
@@ -572,7 +572,7 @@ hipError_t attention_bwd_launch(int dtype, int b, int s, int nh, int nkv, int d,
                                   : dot_launch<bf16, 64>(b, s, nh, o, dout, dvec, st);
     if (e != hipSuccess) return e;
     if (d == 128) return attention_bwd_v3_launch(b, s, nh, nkv, d, qkv, lse, dout, dqkv, dvec, kv_ws, st);
-    return attention_bwd_v2_launch(b, s, nh, d, qkv, lse, dout, dqkv, dvec, st);
+    return attention_bwd16_launch(b, s, nh, d, qkv, lse, dout, dqkv, dvec, st);
   }
   return d == 64 ? bwd_launch<float, 64>(b, s, nh, qkv, o, lse, dout, dqkv, dvec, st)
                  : bwd_launch<float, 128>(b, s, nh, qkv, o, lse, dout, dqkv, dvec, st);

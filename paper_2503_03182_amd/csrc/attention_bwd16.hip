@@ -1,0 +1,403 @@
+// Fused causal attention backward, bf16, head dim 64, on 16x16x32 MFMAs (head
+// dim 128 on 32x32x16 MFMAs: attention_bwd.hip, which states the mathematics).
+//
+// Deterministic: every output element is produced by one wave in a fixed order
+// (no atomics).  A block of 128 rows is owned by a 4-wave workgroup (32 rows per
+// wave) that streams 64-row tiles of the other operands through a two-stage LDS
+// ring.
+//
+// dK/dV (dkdv_block): K and V fragments of the wave's 32 keys in registers; 64-query
+//   tiles of Q, dO, lse and D stream through the ring.  Keys along the MFMA N
+//   dimension (one key of each of two blocks per lane), 32 queries at a time:
+//     S  = Q K^T, dP = dO V^T        (Q, dO rows from LDS)
+//     dV^T += dO^T P, dK^T += Q^T dS (dO^T, Q^T through transposing reads, in
+//                                     the accumulators' query order)
+// dQ (dq_block): Q and dO fragments of the wave's 32 queries plus their lse and D
+//   in registers; 64-key tiles of K and V stream through the ring.  Queries
+//   along N, 32 keys at a time:
+//     S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T
+// Rows past the sequence end load as zeros: their Q and dO rows contribute nothing
+// to dK/dV, and keys past the end lie beyond every query, so the causal mask
+// removes them from dQ.
+//
+// What bounds it: the vector work per score (exp2 at a quarter of the rate, six
+// more operations, packing) next to as many cycles of MFMAs; two waves per SIMD
+// overlap them.  With 16 rows per wave and tiles staged through registers 2 x 1999 x
+// 12 heads took 171 us, here 63 (490 TFLOP/s over five products); 4 x 2048 x 16
+// heads 352 and 160.
+#include "attn16.h"
+
+namespace tps {
+
+namespace b16 {
+
+using namespace a16;
+
+constexpr int D = 64, KS = D / 32, DB = D / 16;
+constexpr int TILE = BT * D * 2;
+constexpr int VEC = 1024;                       // LDS bytes per per-row vector (64 f32 + landing pad)
+constexpr int kDkdvStage = 2 * TILE + 2 * VEC;  // Q, dO, lse, D
+constexpr int kDqStage = 2 * TILE;              // K, V
+
+template <int OFF>
+__device__ __forceinline__ f32x4 ds_f32x4(uint32_t a) {
+  f32x4 v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(a), "i"(OFF));
+  return v;
+}
+
+// 64 consecutive f32 of a per-row vector (lse, D), one buffer-to-LDS instruction
+// (lanes 0-15 carry the 64 values; the other lanes' 16 bytes land in the 768
+// bytes after them).  Entries at or past `rows` read as zeros.
+struct VecSrc {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ void init(const float* base, int rows) { r = rsrc(base, rows * 4); }
+  __device__ __forceinline__ void load(int row0, char* dst, int lane) const {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 16, (uint32_t)(row0 * 4 + lane * 16), 0, 0, 0);
+  }
+};
+
+// dst rows [row][D] += v[2 blocks of 16][DB] * f: lane holds row 16 nb + l % 16, d = 16 db + 4 G + j
+__device__ __forceinline__ void store_rows(bf16* base, int64_t ld, int row0, int rows, const f32x4 (&v)[2][DB], float f,
+                                           int lane) {
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb) {
+    const int row = row0 + 16 * nb + (lane & 15);
+    if (row >= rows) continue;
+    bf16* p = base + (int64_t)row * ld + 4 * (lane >> 4);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      bf16x4 w;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) w[j] = (bf16)(v[nb][db][j] * f);
+      *reinterpret_cast<bf16x4*>(p + 16 * db) = w;
+    }
+  }
+}
+
+struct Args {
+  const bf16 *qkv, *dout;
+  const float *lse, *dvec;
+  bf16* dqkv;
+  int b, s, nh;
+  float scale;
+};
+
+// S (or S^T) and dP (dP^T) of 32 streamed rows x the wave's 32: streamed rows from
+// LDS at x and y (operands of S and dP), the wave's fragments fx, fy.
+template <int ROW0>
+__device__ __forceinline__ void sdp(f32x4 (&sacc)[2][2], f32x4 (&pacc)[2][2], const FragOff<D>& fo, uint32_t x, uint32_t y,
+                                    const bf16x8 (&fx)[2][KS], const bf16x8 (&fy)[2][KS]) {
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) sacc[rb][nb] = pacc[rb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr int N = 4 * KS;   // fragments: operand i % 2, row block (i / 2) % 2, d-step i / 4
+  bf16x8 fr[N];
+  static_for<N>([&](auto ic) {
+    constexpr int i = decltype(ic)::value, w = i % 2, rb = (i / 2) % 2, ks = i / 4;
+    fr[i] = ds_b128<(ROW0 + 16 * rb) * D * 2>(fo.row[ks] + (w ? y : x));
+  });
+  static_for<N>([&](auto ic) {
+    constexpr int i = decltype(ic)::value, w = i % 2, rb = (i / 2) % 2, ks = i / 4;
+    wait_lgkm<N - 1 - i>();
+    pin(fr[i]);
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      if constexpr (w == 0) sacc[rb][nb] = mma(fr[i], fx[nb][ks], sacc[rb][nb]);
+      else pacc[rb][nb] = mma(fr[i], fy[nb][ks], pacc[rb][nb]);
+    }
+  });
+}
+
+__device__ __forceinline__ void dkdv_block(const Args& a, int kblk, int head, int batch, char* smem) {
+  const int s = a.s, nh = a.nh, H = nh * D;
+  const int64_t ld = 3 * (int64_t)H;
+  const int lane = threadIdx.x & 63, G = lane >> 4, c16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int k0 = kblk * 128 + wave * 32;   // first key of this wave
+  const bf16* base = a.qkv + (int64_t)batch * s * ld;
+  bf16x8 kf[2][KS], vf[2][KS];   // B operands: lane holds key 16 kb + c16, d = 32 ks + 8 G .. +8
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    const bf16* krow = base + (int64_t)min(k0 + 16 * kb + c16, s - 1) * ld + H + head * D + 8 * G;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      kf[kb][ks] = load_frag_settled(krow + 32 * ks);
+      vf[kb][ks] = load_frag_settled(krow + H + 32 * ks);
+    }
+  }
+  // query tiles from the one holding this workgroup's first key to the end
+  const int tb = kblk * 128 / BT;
+  const int np = (s + BT - 1) / BT - tb;
+
+  TileSrc<D, 4> qsrc, dsrc;
+  qsrc.init(base + head * D, ld, s, wave, lane);
+  dsrc.init(a.dout + (int64_t)batch * s * H + head * D, H, s, wave, lane);
+  VecSrc lsrc, vsrc;
+  lsrc.init(a.lse + ((int64_t)batch * nh + head) * s, s);
+  vsrc.init(a.dvec + ((int64_t)batch * nh + head) * s, s);
+  auto load_tile = [&](int t, int st) {
+    char* p = smem + st * kDkdvStage;
+    qsrc.load(t * BT, p);
+    dsrc.load(t * BT, p + TILE);
+    if (wave == 0) {
+      lsrc.load(t * BT, p + 2 * TILE, lane);
+      vsrc.load(t * BT, p + 2 * TILE + VEC, lane);
+    }
+  };
+  constexpr int LPT = 2 * TileSrc<D, 4>::IPW;
+  FragOff<D> fo;
+  fo.init(lds_u32(smem), lane);
+  const uint32_t vbase = lds_u32(smem) + 2 * TILE + 16 * G;   // lse of row 4 G of the stage-0 tile
+
+  f32x4 dk[2][DB], dv[2][DB];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) dk[kb][db] = dv[kb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float sl2 = a.scale * kLog2e;
+
+  auto tile = [&](int t, int st, auto diag_c) {
+    constexpr bool DIAG = decltype(diag_c)::value;
+    const uint32_t qo = st * kDkdvStage, dO = qo + TILE;
+    static_for<2>([&](auto uc) {   // 32 queries at a time
+      constexpr int u = decltype(uc)::value;
+      // lse and D of the rows this lane holds: 32 u + 16 rb + 4 G + j
+      f32x4 lv[2], dd[2];
+      static_for<2>([&](auto rc) {
+        constexpr int rb = decltype(rc)::value, o = (32 * u + 16 * rb) * 4;
+        lv[rb] = ds_f32x4<o>(vbase + qo);
+        dd[rb] = ds_f32x4<o + VEC>(vbase + qo);
+      });
+      f32x4 sacc[2][2], pacc[2][2];
+      sdp<32 * u>(sacc, pacc, fo, qo, dO, kf, vf);
+      // the transposed fragments come in beside the vector work: operand (dO^T, Q^T) i % 2, d block i / 2
+      constexpr int N = 2 * DB, A = 7;
+      s16x4 lo[N], hi[N];
+      auto read_t = [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        read_cols<D, 32 * u * D * 2>(lo[i], hi[i], fo.col[i / 2] + (i % 2 ? qo : dO));
+      };
+      static_for<A>([&](auto ic) { read_t(ic); });
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        pin(lv[rb]);
+        pin(dd[rb]);
+      }
+      bf16x8 pb[2], sb[2];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        const int thr = k0 + 16 * kb + c16 - 4 * G - t * BT;   // query 32 u + 16 rb + j is before the key if < thr
+        float p[2][4], d[2][4];
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[rb][kb][j], sl2, -lv[rb][j] * kLog2e));
+            if constexpr (DIAG) {
+              if (32 * u + 16 * rb + j < thr) pv = 0.f;
+            }
+            p[rb][j] = pv;
+            d[rb][j] = pv * (pacc[rb][kb][j] - dd[rb][j]);
+          }
+        pb[kb] = frag_acc(p[0], p[1]);
+        sb[kb] = frag_acc(d[0], d[1]);
+      }
+      static_for<N>([&](auto ic) {
+        constexpr int i = decltype(ic)::value, w = i % 2, db = i / 2;
+        constexpr int issued = (i + A < N) ? i + A : N;
+        wait_lgkm<2 * (issued - i - 1)>();
+        bf16x8 f = join(lo[i], hi[i]);
+        pin(f);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+          if constexpr (w == 0) dv[kb][db] = mma(f, pb[kb], dv[kb][db]);
+          else dk[kb][db] = mma(f, sb[kb], dk[kb][db]);
+        }
+        if constexpr (i + A < N) read_t(std::integral_constant<int, i + A>{});
+      });
+    });
+  };
+
+  if (np > 0) load_tile(tb, 0);
+  if (np > 1) {
+    load_tile(tb + 1, 1);
+    if (wave == 0) wait_vmcnt<LPT + 2>();   // the first tile landed
+    else wait_vmcnt<LPT>();
+  } else {
+    wait_vmcnt<0>();
+  }
+  lds_barrier();
+  // hand the stage of trip `it` back: the next tile has landed, every wave is
+  // done with this one
+  auto trip_end = [&](int it) {
+    wait_vmcnt<0>();
+    lds_barrier();
+    if (it + 2 < np) load_tile(tb + it + 2, it & 1);
+  };
+  // The wave skips the tiles before the one holding its first key, then takes
+  // the tiles where some query precedes some key (masked), then the rest
+  const int n_skip = min(max(k0 / BT - tb, 0), np);
+  const int n_diag = min(max((k0 + 30) / BT + 1 - tb, n_skip), np);
+  int it = 0;
+  for (; it < n_skip; ++it) trip_end(it);
+  for (; it < n_diag; ++it) {
+    tile(tb + it, it & 1, std::true_type{});
+    trip_end(it);
+  }
+  for (; it < np; ++it) {
+    tile(tb + it, it & 1, std::false_type{});
+    trip_end(it);
+  }
+  bf16* out = a.dqkv + (int64_t)batch * s * ld + head * D;
+  store_rows(out + H, ld, k0, s, dk, a.scale, lane);
+  store_rows(out + 2 * H, ld, k0, s, dv, 1.f, lane);
+}
+
+__device__ __forceinline__ void dq_block(const Args& a, int qblk, int head, int batch, char* smem) {
+  const int s = a.s, nh = a.nh, H = nh * D;
+  const int64_t ld = 3 * (int64_t)H;
+  const int lane = threadIdx.x & 63, G = lane >> 4, c16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q0 = qblk * 128 + wave * 32;   // first query of this wave
+  const bf16* base = a.qkv + (int64_t)batch * s * ld;
+  bf16x8 qf[2][KS], df[2][KS];   // lane holds query 16 qb + c16
+  float lse2[2], dot[2];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const int q = min(q0 + 16 * qb + c16, s - 1);
+    const bf16* qrow = base + (int64_t)q * ld + head * D + 8 * G;
+    const bf16* drow = a.dout + ((int64_t)batch * s + q) * H + head * D + 8 * G;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      qf[qb][ks] = load_frag_settled(qrow + 32 * ks);
+      df[qb][ks] = load_frag_settled(drow + 32 * ks);
+    }
+    lse2[qb] = a.lse[((int64_t)batch * nh + head) * s + q] * kLog2e;
+    dot[qb] = a.dvec[((int64_t)batch * nh + head) * s + q];
+  }
+  const int np = min(qblk * 128 + 127, s - 1) / BT + 1;   // key tiles up to the workgroup's last query
+  const int wave_last = min(q0 + 31, s - 1) / BT;
+
+  TileSrc<D, 4> ksrc, vsrc;
+  ksrc.init(base + H + head * D, ld, s, wave, lane);
+  vsrc.init(base + 2 * H + head * D, ld, s, wave, lane);
+  auto load_tile = [&](int t, int st) {
+    ksrc.load(t * BT, smem + st * kDqStage);
+    vsrc.load(t * BT, smem + st * kDqStage + TILE);
+  };
+  constexpr int LPT = 2 * TileSrc<D, 4>::IPW;
+  FragOff<D> fo;
+  fo.init(lds_u32(smem), lane);
+  f32x4 dq[2][DB];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) dq[qb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float sl2 = a.scale * kLog2e;
+
+  auto tile = [&](int t, int st, auto diag_c) {
+    constexpr bool DIAG = decltype(diag_c)::value;
+    const uint32_t ko = st * kDqStage, vo = ko + TILE;
+    static_for<2>([&](auto uc) {   // 32 keys at a time
+      constexpr int u = decltype(uc)::value;
+      f32x4 sacc[2][2], pacc[2][2];
+      sdp<32 * u>(sacc, pacc, fo, ko, vo, qf, df);
+      s16x4 lo[DB], hi[DB];
+      static_for<DB>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        read_cols<D, 32 * u * D * 2>(lo[i], hi[i], fo.col[i] + ko);
+      });
+      bf16x8 sb[2];
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        const int thr = q0 + 16 * qb + c16 - 4 * G - t * BT;   // key 32 u + 16 kb + j is past the query if > thr
+        float d[2][4];
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[kb][qb][j], sl2, -lse2[qb]));
+            if constexpr (DIAG) {
+              if (32 * u + 16 * kb + j > thr) pv = 0.f;
+            }
+            d[kb][j] = pv * (pacc[kb][qb][j] - dot[qb]);
+          }
+        sb[qb] = frag_acc(d[0], d[1]);
+      }
+      static_for<DB>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        wait_lgkm<2 * (DB - 1 - i)>();
+        bf16x8 f = join(lo[i], hi[i]);
+        pin(f);
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) dq[qb][i] = mma(f, sb[qb], dq[qb][i]);
+      });
+    });
+  };
+
+  load_tile(0, 0);
+  if (np > 1) {
+    load_tile(1, 1);
+    wait_vmcnt<LPT>();   // the first tile landed
+  } else {
+    wait_vmcnt<0>();
+  }
+  lds_barrier();
+  auto trip_end = [&](int it) {
+    wait_vmcnt<0>();
+    lds_barrier();
+    if (it + 2 < np) load_tile(it + 2, it & 1);
+  };
+  // a prefix of the tiles (up to the one holding the wave's last query), those
+  // crossing the diagonal last, then barrier-only trips while the others finish
+  const int n_comp = max(0, min(np, wave_last + 1));
+  const int n_plain = max(0, min(n_comp, (q0 + 1) / BT));   // tiles whose last key <= q0
+  int it = 0;
+  for (; it < n_plain; ++it) {
+    tile(it, it & 1, std::false_type{});
+    trip_end(it);
+  }
+  for (; it < n_comp; ++it) {
+    tile(it, it & 1, std::true_type{});
+    trip_end(it);
+  }
+  for (; it < np; ++it) trip_end(it);
+  store_rows(a.dqkv + (int64_t)batch * s * ld + head * D, ld, q0, s, dq, a.scale, lane);
+}
+
+}  // namespace b16
+
+// Every 128-row block has a dK/dV and a dQ workgroup, launched heaviest first (the
+// first key blocks, the last query blocks): INTER alternates the two kinds, else
+// all dK/dV blocks come first.
+template <bool INTER>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
+void attn_bwd16_kernel(b16::Args a) {
+#ifdef __HIP_DEVICE_COMPILE__
+  __shared__ __attribute__((aligned(1024))) char smem[2 * b16::kDkdvStage];
+  const int nhb = a.nh * a.b, n = (a.s + 127) / 128;
+  const int idx = blockIdx.x, k = idx / nhb, head = idx % a.nh, batch = (idx / a.nh) % a.b;
+  const bool dq = INTER ? k & 1 : k >= n;
+  const int rank = INTER ? k >> 1 : k % n;
+  if (dq) b16::dq_block(a, n - 1 - rank, head, batch, smem);
+  else b16::dkdv_block(a, rank, head, batch, smem);
+#endif
+}
+
+hipError_t attention_bwd16_launch(int b, int s, int nh, int d, const void* qkv, const float* lse, const void* dout,
+                                  void* dqkv, const float* dvec, hipStream_t st) {
+  if (d != b16::D) return hipErrorInvalidValue;
+  const b16::Args a{(const bf16*)qkv, (const bf16*)dout, lse, dvec, (bf16*)dqkv, b, s, nh, 1.0f / sqrtf((float)d)};
+  // Two workgroups fit a CU: while the grid is resident at once the kinds
+  // alternate, so that neighbours on a CU differ (2 x 1000 x 16 heads: 33 against 38
+  // us); larger grids take the dearer dK/dV blocks first (4096 x 16 heads: 142
+  // against 155 us, others within 3% either way).
+  const int grid = 2 * ((s + 127) / 128) * nh * b;
+  if (grid <= 512) hipLaunchKernelGGL((attn_bwd16_kernel<true>), dim3(grid), dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((attn_bwd16_kernel<false>), dim3(grid), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace tps

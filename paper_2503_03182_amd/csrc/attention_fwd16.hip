@@ -1,0 +1,316 @@
+// Fused causal attention forward, bf16, head dim 64, on 16x16x32 MFMAs (head dim
+// 128 on 32x32x16 MFMAs: attention_fwd.hip; this kernel at 128 ran within 1% of it).
+//
+// Work split.  A workgroup of QW x PARTS waves owns 32 QW consecutive queries of
+// one (batch, head) and splits both ways: wave w takes the 32 queries of slice
+// w % QW against the key tiles of part w / QW (part 0: the first ceil(n / 2) of
+// the block's n key tiles, part 1: the rest, which hold the diagonal), the parts
+// merged in a fixed order through LDS at the end.  Workgroups are launched
+// heaviest first.
+//
+// Per 64-key tile and wave (transposed formulation, queries along MFMA N, two
+// blocks of 16):
+//   S^T[key, q]  = K Q^T      K from LDS (ds_read_b128), each fragment feeding
+//                             both query blocks; Q^T fragments in registers;
+//   online softmax over keys for each query: a lane holds one query of each
+//                             block and 4 keys of each 16-key block, its
+//                             partners l ^ 16, l ^ 32, l ^ 48 the others;
+//   O^T[d, q]   += V^T P^T    P^T straight from the S^T accumulators, V^T from
+//                             LDS through transposing reads in their key order.
+//
+// What bounds it: the softmax's vector work (per tile and wave 32 exp2 at a
+// quarter of the rate, and as many FMAs, maxima and adds, about 900 cycles)
+// next to 512 cycles of MFMAs; three waves per SIMD overlap them where the keys
+// are not split (two: 10% slower, four do not fit the registers).  4 x 2048 x 16 heads: 135 us with 16
+// queries per wave and tiles staged through registers, 57 us (603 TFLOP/s) here.
+//
+// Data movement.  Each key part streams its K and V tiles global -> LDS by buffer
+// loads that write LDS directly, into its own two-stage ring; LDS reads are
+// inline assembly with explicit lgkmcnt waits; one barrier per tile hands the
+// stage of tile t back for tile t + 2.
+//
+// Numerics: scores are scaled into the log2 domain (scale * log2 e), the softmax
+// uses exp2; lse is returned in natural log.  Causal masking runs only on tiles
+// that cross the diagonal; O is rescaled only when some lane's running max grew
+// (the multiplier is exactly 1 otherwise).  Every reduction runs in a fixed
+// order, so results are bitwise reproducible.
+#include "attn16.h"
+
+namespace tps {
+
+template <int D, int QW, int PARTS>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * QW * PARTS, 64 * QW * PARTS),
+                          amdgpu_waves_per_eu(PARTS == 1 ? 3 : 2, PARTS == 1 ? 3 : 2)))
+void attn_fwd16_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ o, float* __restrict__ lse, int b, int s,
+                       int nh, float scale, int nkv) {
+#ifdef __HIP_DEVICE_COMPILE__
+  using namespace a16;
+  constexpr int BQ = 32 * QW;           // queries per workgroup
+  constexpr int TILE = BT * D * 2;
+  constexpr int STAGE = 2 * TILE;       // K and V
+  constexpr int RING = 2 * STAGE;       // one key part's two stages
+  constexpr int KS = D / 32, DB = D / 16;
+  constexpr int PARK = (2 * DB * 4 + 4) * 64 * 4;   // merge: O, m, l of a slice
+  static_assert(PARTS == 1 || PARTS == 2, "key parts");
+  constexpr int LDS = PARTS * RING > (PARTS - 1) * QW * PARK ? PARTS * RING : (PARTS - 1) * QW * PARK;
+  __shared__ __attribute__((aligned(1024))) char smem[LDS];
+
+  // qkv rows: q of nh heads | k, v of nkv heads; query head n reads
+  // key/value head n / (nh / nkv) (nkv == nh: plain multi-head)
+  const int H = nh * D, HK = nkv * D;
+  const int64_t ld = (int64_t)H + 2 * HK;
+  const int nqb = (s + BQ - 1) / BQ;
+  const int idx = blockIdx.x;
+  const int head = idx % nh;
+  const int kvh = head / (nh / nkv);
+  const int batch = (idx / nh) % b;
+  const int qblk = nqb - 1 - idx / (nh * b);   // heaviest blocks first
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int slice = wave % QW, part = wave / QW;
+  const int q0 = qblk * BQ + slice * 32;       // first query of this wave
+  const int G = lane >> 4, c16 = lane & 15;
+
+  const bf16* base = qkv + (int64_t)batch * s * ld;
+  const int nt = (min(qblk * BQ + BQ, s) - 1) / BT + 1;   // key tiles of the block
+  const int nt0 = PARTS == 1 ? nt : (nt + 1) / 2;
+  const int tb = part ? nt0 : 0;             // first tile of this part
+  const int np = part ? nt - nt0 : nt0;      // tiles of this part
+  const int nit = nt0;                       // loop trips (both parts, for the barriers)
+  const int wave_last = min(q0 + 31, s - 1) / BT;
+
+  // Q^T fragments (B operand): lane holds query 16 qb + c16, d = 32 ks + 8 G .. +8
+  bf16x8 qf[2][KS];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const bf16* qrow = base + (int64_t)min(q0 + 16 * qb + c16, s - 1) * ld + head * D + 8 * G;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = load_frag_settled(qrow + 32 * ks);
+  }
+
+  TileSrc<D, QW> ksrc, vsrc;
+  ksrc.init(base + H + kvh * D, ld, s, slice, lane);
+  vsrc.init(base + H + HK + kvh * D, ld, s, slice, lane);
+  char* const ring = smem + part * RING;
+  auto load_tile = [&](int t, int st) {
+    ksrc.load(t * BT, ring + st * STAGE);
+    vsrc.load(t * BT, ring + st * STAGE + TILE);
+  };
+  constexpr int LPT = 2 * TileSrc<D, QW>::IPW;   // load instructions per wave per tile
+  FragOff<D> fo;
+  fo.init(lds_u32(ring), lane);
+
+  f32x4 oacc[2][DB];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[qb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+  const float sl2 = scale * kLog2e;
+
+  // one 64-key tile in stage st; DIAG: some key of the tile lies past some query
+  auto tile = [&](int t, int st, auto diag_c) {
+    constexpr bool DIAG = decltype(diag_c)::value;
+    const uint32_t kst = st * STAGE, vst = kst + TILE;
+    // ---- S^T = K Q^T: 4 key blocks x KS d-steps, each K fragment for both query blocks
+    f32x4 sacc[2][4];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) sacc[qb][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int NK = 4 * KS;   // K fragments
+    bf16x8 kf[NK];
+    auto read_k = [&](auto ic) {
+      constexpr int i = decltype(ic)::value, kb = i % 4, ks = i / 4;
+      kf[i] = ds_b128<kb * 16 * D * 2>(fo.row[ks] + kst);
+    };
+    constexpr int KA = 8;        // in flight
+    static_for<KA>([&](auto ic) { read_k(ic); });
+    static_for<NK>([&](auto ic) {
+      constexpr int i = decltype(ic)::value, kb = i % 4, ks = i / 4;
+      constexpr int issued = (i + KA < NK) ? i + KA : NK;
+      wait_lgkm<issued - i - 1>();
+      pin(kf[i]);
+      sacc[0][kb] = mma(kf[i], qf[0][ks], sacc[0][kb]);
+      sacc[1][kb] = mma(kf[i], qf[1][ks], sacc[1][kb]);
+      if constexpr (i + KA < NK) read_k(std::integral_constant<int, i + KA>{});
+    });
+    // the first V fragments come in beside the softmax
+    constexpr int NV = 2 * DB;   // V fragments: 32-key step u = i / DB, d block i % DB
+    s16x4 vlo[NV], vhi[NV];
+    auto read_v = [&](auto ic) {
+      constexpr int i = decltype(ic)::value, u = i / DB, db = i % DB;
+      read_cols<D, 32 * u * D * 2>(vlo[i], vhi[i], fo.col[db] + vst);
+    };
+    constexpr int VA = 7;
+    static_for<VA>([&](auto ic) { read_v(ic); });
+
+    // ---- online softmax on raw scores (the scale is positive, so the max
+    // commutes with it; it enters the exponent's FMA)
+    bf16x8 pb[2][2];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      if constexpr (DIAG) {
+        const int thr = q0 + 16 * qb + c16 - 4 * G - t * BT;   // key 16 kb + j of this lane is past the query if > thr
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (16 * kb + j > thr) sacc[qb][kb][j] = -INFINITY;
+      }
+      float mx = sacc[qb][0][0];
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mx = fmaxf(mx, sacc[qb][kb][j]);
+      mx = quad_max(mx);
+      const float m_new = fmaxf(m_run[qb], mx * sl2);
+      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+      // rescale only when some lane's running max grew (alpha is 1 otherwise)
+      const bool grew = m_new > m_run[qb];
+      const float alpha = grew ? __builtin_amdgcn_exp2f(m_run[qb] - m_use) : 1.f;
+      m_run[qb] = m_new;
+      float ls = 0.f;
+      float x[4][4];
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          x[kb][j] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[qb][kb][j], sl2, -m_use));
+          ls += x[kb][j];
+        }
+      l_run[qb] = l_run[qb] * alpha + ls;
+      if (__builtin_amdgcn_ballot_w64(grew) != 0) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) oacc[qb][db][j] *= alpha;
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) pb[qb][u] = frag_acc(x[2 * u], x[2 * u + 1]);
+    }
+
+    // ---- O^T += V^T P^T: 2 key steps x DB d blocks, each V fragment for both query blocks
+    static_for<NV>([&](auto ic) {
+      constexpr int i = decltype(ic)::value, u = i / DB, db = i % DB;
+      constexpr int issued = (i + VA < NV) ? i + VA : NV;
+      wait_lgkm<2 * (issued - i - 1)>();
+      bf16x8 vf = join(vlo[i], vhi[i]);
+      pin(vf);
+      oacc[0][db] = mma(vf, pb[0][u], oacc[0][db]);
+      oacc[1][db] = mma(vf, pb[1][u], oacc[1][db]);
+      if constexpr (i + VA < NV) read_v(std::integral_constant<int, i + VA>{});
+    });
+  };
+
+  // prologue: the first two tiles of each part
+  if (np > 0) load_tile(tb, 0);
+  if (np > 1) {
+    load_tile(tb + 1, 1);
+    wait_vmcnt<LPT>();   // the first tile landed
+  } else {
+    wait_vmcnt<0>();
+  }
+  lds_barrier();
+  // hand the stage of trip `it` back: the next tile (the only loads in
+  // flight) has landed and every wave is done with this one
+  auto trip_end = [&](int it) {
+    wait_vmcnt<0>();
+    lds_barrier();
+    if (it + 2 < np) load_tile(tb + it + 2, it & 1);
+  };
+  // The wave computes a prefix of the part's tiles (up to the one holding its
+  // last query), the tiles that cross the diagonal last; one loop per kind
+  // and a barrier-only loop for the remaining trips keep the accumulators in
+  // place (a join of paths inside one loop makes the compiler copy them).
+  const int n_comp = max(0, min(np, wave_last + 1 - tb));
+  const int n_plain = max(0, min(n_comp, (q0 + 1) / BT - tb));   // tiles whose last key <= q0
+  int it = 0;
+  for (; it < n_plain; ++it) {
+    tile(tb + it, it & 1, std::false_type{});
+    trip_end(it);
+  }
+  for (; it < n_comp; ++it) {
+    tile(tb + it, it & 1, std::true_type{});
+    trip_end(it);
+  }
+  for (; it < nit; ++it) trip_end(it);
+
+  // ---- merge the key parts of each query slice through LDS (ring memory is
+  // free after the loop's last barrier): part 1 parks m, l and O^T
+  if constexpr (PARTS == 2) {
+    float* park = reinterpret_cast<float*>(smem) + slice * (PARK / 4);
+    if (part == 1) {
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) park[((qb * DB + db) * 4 + j) * 64 + lane] = oacc[qb][db][j];
+        park[(8 * DB + 2 * qb) * 64 + lane] = m_run[qb];
+        park[(8 * DB + 2 * qb + 1) * 64 + lane] = l_run[qb];
+      }
+    }
+    __syncthreads();
+    if (part == 1) return;
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      const float m1 = park[(8 * DB + 2 * qb) * 64 + lane], l1 = park[(8 * DB + 2 * qb + 1) * 64 + lane];
+      const float m = fmaxf(m_run[qb], m1);   // part 0 always holds key 0 <= q: m is finite
+      const float a0 = __builtin_amdgcn_exp2f(m_run[qb] - m), a1 = __builtin_amdgcn_exp2f(m1 - m);
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          oacc[qb][db][j] = oacc[qb][db][j] * a0 + park[((qb * DB + db) * 4 + j) * 64 + lane] * a1;
+      l_run[qb] = l_run[qb] * a0 + l1 * a1;
+      m_run[qb] = m;
+    }
+  }
+
+  // ---- normalise and store: lane holds O^T[16 db + 4 G + j][16 qb + c16]
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const int q = q0 + 16 * qb + c16;
+    const float l_tot = quad_sum(l_run[qb]);
+    if (q < s) {
+      const float inv = 1.f / l_tot;
+      bf16* orow = o + ((int64_t)batch * s + q) * H + head * D + 4 * G;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        bf16x4 w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = (bf16)(oacc[qb][db][j] * inv);
+        *reinterpret_cast<bf16x4*>(orow + 16 * db) = w;
+      }
+      if (lse != nullptr && G == 0) lse[((int64_t)batch * nh + head) * s + q] = m_run[qb] * kLn2 + logf(l_tot);
+    }
+  }
+#endif
+}
+
+hipError_t attention_fwd16_launch(int b, int s, int nh, int nkv, int d, const void* qkv, void* o, float* lse,
+                                  hipStream_t st) {
+  if (d != 64 || nkv <= 0 || nh % nkv != 0) return hipErrorInvalidValue;
+  const float scale = 1.0f / sqrtf((float)d);
+  const bf16* x = (const bf16*)qkv;
+  // Blocks of 128 queries without splitting the keys when they fill the chip
+  // twice and the longest chain of key tiles (s / 64) is short next to the whole
+  // work (8 x 1024 x 12 heads: 27 against 34 us; 1 x 4096 x 16 heads, 512 blocks
+  // with chains of 64 tiles: 66 against 58 us); below 320 blocks of 64 queries
+  // (2 x 1000 x 16 heads: 13 against 16 us).
+  const int n128 = (s + 127) / 128 * nh * b;
+  if (n128 >= 512 && n128 >= s / 6) {
+    hipLaunchKernelGGL((attn_fwd16_kernel<64, 4, 1>), dim3(n128), dim3(256), 0, st, x, (bf16*)o, lse, b, s, nh, scale,
+                       nkv);
+  } else if (n128 >= 320) {
+    hipLaunchKernelGGL((attn_fwd16_kernel<64, 4, 2>), dim3(n128), dim3(512), 0, st, x, (bf16*)o, lse, b, s, nh, scale,
+                       nkv);
+  } else {
+    hipLaunchKernelGGL((attn_fwd16_kernel<64, 2, 2>), dim3((s + 63) / 64 * nh * b), dim3(256), 0, st, x, (bf16*)o, lse,
+                       b, s, nh, scale, nkv);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace tps

@@ -1,0 +1,162 @@
+// Shared pieces of the bf16 attention kernels on 16x16x32 MFMAs: the LDS layout
+// of a 64-row tile of one head, its buffer-to-LDS loads, and the per-lane LDS
+// offsets of the two fragment kinds the kernels read from such a tile.
+//
+// Tile layout: 64 rows (keys or queries) x D bf16; 16-byte chunks XOR-swizzled
+// per row so that both reads are free of bank conflicts:
+//   ds_read_b128 (16 consecutive rows at one chunk per pass), and
+//   ds_read_b64_tr_b16 (8 consecutive rows x 2 chunks per pass of 32 lanes).
+// D = 128 (256-byte rows): f(r) = 2 (r & 7) + ((r >> 3) & 1), a permutation of
+// the 16 chunks over 16 aligned rows whose pair f >> 1 differs over 8.  D = 64
+// (128-byte rows, odd rows in the other bank half): f(r) = 2 ((r >> 1) & 3) +
+// ((r >> 3) & 1), the same over the even (odd) rows.
+#pragma once
+#include "gemm_lds.h"
+#include "kernels.h"
+#include "tps_device.h"
+
+namespace tps {
+namespace a16 {
+
+using gl::ds_b128;
+using gl::ds_tr16;
+using gl::lds_barrier;
+using gl::lds_u32;
+using gl::pin;
+using gl::static_for;
+using gl::wait_lgkm;
+using gl::wait_vmcnt;
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(8))) short s16x8;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+
+constexpr int BT = 64;   // rows per tile
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLn2 = 0.6931471805599453f;
+
+template <int D>
+__device__ __forceinline__ int swz(int r) {
+  return (((D == 128 ? r & 7 : (r >> 1) & 3)) << 1) | ((r >> 3) & 1);
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, bytes, 0x00020000);
+}
+
+__device__ __forceinline__ f32x4 mma(const bf16x8& a, const bf16x8& b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// max (sum) over the four lanes l, l ^ 16, l ^ 32, l ^ 48, in every lane
+__device__ __forceinline__ float quad_max(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// Rows of one head's D columns in a [rows][ld] bf16 matrix, copied into LDS
+// tiles by D / 8 one-KB buffer-to-LDS instructions shared by NW waves.  The
+// buffer is the tile itself (a matrix may exceed the 32 bits of a buffer
+// offset) and ends at its last row: rows at or past `rows` read as zeros.
+template <int D, int NW>
+struct TileSrc {
+  static constexpr int RPI = 1024 / (D * 2);            // rows per instruction
+  static constexpr int INST = BT / RPI, IPW = INST / NW;
+  static constexpr int PER = 16 / RPI;                  // the swizzle repeats every 16 rows
+  static constexpr int NV = IPW < PER ? IPW : PER;
+  static_assert(INST % NW == 0 && (IPW % PER == 0 || PER % IPW == 0), "instructions per wave");
+  const char* base;
+  uint32_t voff[NV];
+  uint32_t ld2;
+  int w, rows;
+  __device__ __forceinline__ void init(const bf16* base_, int64_t ld, int rows_, int wave, int lane) {
+    ld2 = (uint32_t)(ld * 2);
+    w = wave;
+    base = reinterpret_cast<const char*>(base_);
+    rows = rows_;
+    constexpr int CPR = D / 8;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int row = (w * IPW + j) * RPI + lane / CPR;
+      const int c = (lane % CPR) ^ swz<D>(row);
+      voff[j] = (uint32_t)row * ld2 + (uint32_t)c * 16;
+    }
+  }
+  __device__ __forceinline__ void load(int row0, char* tile) const {
+    const int n = min(rows - row0, BT);
+    const __amdgpu_buffer_rsrc_t r = rsrc(base + (uint64_t)(uint32_t)row0 * ld2, n > 0 ? (n - 1) * (int)ld2 + D * 2 : 0);
+#pragma unroll
+    for (int j = 0; j < IPW; ++j) {
+      const uint32_t v = voff[j % NV] + (uint32_t)((j / NV) * NV * RPI) * ld2;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(tile + (w * IPW + j) * 1024), 16, v, 0, 0, 0);
+    }
+  }
+};
+
+// Per-lane LDS offsets inside a tile (G = l / 16, s = l % 16).
+//  Row fragment (d contiguous) of 16-row block rb and d-step ks: row 16 rb + s,
+//  d = 32 ks + 8 G .. +8; rb is an immediate.
+//  Transposed fragment (row index contiguous) of d block db and 32-row step u:
+//  lane l holds column 16 db + s at rows 32 u + 4 G + i (i < 4: lo) and 32 u +
+//  16 + 4 G + i (hi), the order in which two 16 x 16 accumulators hold rows; u
+//  is an immediate.
+template <int D>
+struct FragOff {
+  static constexpr int ROWB = D * 2;
+  uint32_t row[D / 32];
+  uint32_t col[D / 16];
+  __device__ __forceinline__ void init(uint32_t lds, int lane) {
+    const int G = lane >> 4, s = lane & 15;
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) row[ks] = lds + s * ROWB + (((4 * ks + G) ^ swz<D>(s)) << 4);
+    const int r = 4 * G + (s >> 2);
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db) {
+      const int c = 16 * db + 4 * (s & 3);
+      col[db] = lds + r * ROWB + (((c >> 3) ^ swz<D>(r)) << 4) + (c & 7) * 2;
+    }
+  }
+};
+// the swizzle repeats every 16 rows: the hi half is 16 rows on
+template <int D, int OFF>
+__device__ __forceinline__ void read_cols(s16x4& lo, s16x4& hi, uint32_t a) {
+  lo = ds_tr16<OFF>(a);
+  hi = ds_tr16<OFF + 16 * D * 2>(a);
+}
+__device__ __forceinline__ bf16x8 join(const s16x4& lo, const s16x4& hi) {
+  s16x8 w = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  return *reinterpret_cast<bf16x8*>(&w);
+}
+
+// B operand of a 32-row step from two accumulators (rows 4 G + i and 16 + 4 G + i)
+__device__ __forceinline__ bf16x8 frag_acc(const float* lo, const float* hi) {
+  bf16x8 f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f[i] = (bf16)lo[i];
+    f[4 + i] = (bf16)hi[i];
+  }
+  return f;
+}
+
+// 8 bf16 of one lane, read from global memory and consumed before the tile
+// loop (the wait for the load is placed here, so no wait inside the loop has
+// to drain the tile loads issued after it).
+__device__ __forceinline__ bf16x8 load_frag_settled(const bf16* p) {
+  const u32x4 w = *reinterpret_cast<const u32x4*>(p);
+  bf16x8 f = *reinterpret_cast<const bf16x8*>(&w);
+  asm volatile("" ::"v"(f));
+  return f;
+}
+
+}  // namespace a16
+}  // namespace tps

@@ -52,9 +52,9 @@ hipError_t attention_bwd_launch(int dtype, int b, int s, int nh, int nkv, int d,
                                 const float* lse, const void* dout, void* dqkv, float* dvec, void* kv_ws,
                                 hipStream_t st);
 
-// bf16 kernels on 16x16x32 MFMAs with paired causal blocks (attention_v2.hip)
-hipError_t attention_fwd_v2_launch(int b, int s, int nh, int d, const void* qkv, void* o, float* lse,
-                                   hipStream_t st);
+// bf16, head dim 64: 32 queries per wave on 16x16x32 MFMAs (attention_fwd16.hip)
+hipError_t attention_fwd16_launch(int b, int s, int nh, int nkv, int d, const void* qkv, void* o, float* lse,
+                                  hipStream_t st);
 // bf16, head dim 128: 32 queries per wave on 32x32x16 MFMAs, key tiles split
 // in two parts per workgroup on small grids (attention_fwd.hip); the name of
 // the kernel instance a shape launches
@@ -64,8 +64,9 @@ const char* attention_fwd_v3_name(int b, int s, int nh);
 // bf16, head dim 128: dK/dV by 32-key waves, dQ by 32-query waves (attention_bwd.hip)
 hipError_t attention_bwd_v3_launch(int b, int s, int nh, int nkv, int d, const void* qkv, const float* lse,
                                    const void* dout, void* dqkv, const float* dvec, void* kv_ws, hipStream_t st);
-hipError_t attention_bwd_v2_launch(int b, int s, int nh, int d, const void* qkv, const float* lse, const void* dout,
-                                   void* dqkv, const float* dvec, hipStream_t st);
+// bf16, head dim 64 (attention_bwd16.hip)
+hipError_t attention_bwd16_launch(int b, int s, int nh, int d, const void* qkv, const float* lse, const void* dout,
+                                  void* dqkv, const float* dvec, hipStream_t st);
 
 hipError_t layernorm_fwd_launch(int dtype, int rows, int cols, const void* x, const void* gamma,
                                 const void* beta, float eps, void* out, float* mean, float* rstd,
