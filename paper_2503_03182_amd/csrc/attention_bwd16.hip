@@ -58,8 +58,9 @@ struct VecSrc {
 };
 
 // dst rows [row][D] += v[2 blocks of 16][DB] * f: lane holds row 16 nb + l % 16, d = 16 db + 4 G + j
-__device__ __forceinline__ void store_rows(bf16* base, int64_t ld, int row0, int rows, const f32x4 (&v)[2][DB], float f,
+__device__ __forceinline__ void store_rows(bf16* base, int64_t ld, int row0, int rows, f32x4 (&v)[2][DB], float f,
                                            int lane) {
+  mma_settle();
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
     const int row = row0 + 16 * nb + (lane & 15);
@@ -67,6 +68,7 @@ __device__ __forceinline__ void store_rows(bf16* base, int64_t ld, int row0, int
     bf16* p = base + (int64_t)row * ld + 4 * (lane >> 4);
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
+      pin(v[nb][db]);
       bf16x4 w;
 #pragma unroll
       for (int j = 0; j < 4; ++j) w[j] = (bf16)(v[nb][db][j] * f);
@@ -88,10 +90,6 @@ struct Args {
 template <int ROW0>
 __device__ __forceinline__ void sdp(f32x4 (&sacc)[2][2], f32x4 (&pacc)[2][2], const FragOff<D>& fo, uint32_t x, uint32_t y,
                                     const bf16x8 (&fx)[2][KS], const bf16x8 (&fy)[2][KS]) {
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) sacc[rb][nb] = pacc[rb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
   constexpr int N = 4 * KS;   // fragments: operand i % 2, row block (i / 2) % 2, d-step i / 4
   bf16x8 fr[N];
   static_for<N>([&](auto ic) {
@@ -104,10 +102,23 @@ __device__ __forceinline__ void sdp(f32x4 (&sacc)[2][2], f32x4 (&pacc)[2][2], co
     pin(fr[i]);
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
-      if constexpr (w == 0) sacc[rb][nb] = mma(fr[i], fx[nb][ks], sacc[rb][nb]);
-      else pacc[rb][nb] = mma(fr[i], fy[nb][ks], pacc[rb][nb]);
+      f32x4& c = w == 0 ? sacc[rb][nb] : pacc[rb][nb];
+      const bf16x8& f = w == 0 ? fx[nb][ks] : fy[nb][ks];
+      if constexpr (ks == 0) c = mma(fr[i], f, f32x4{0.f, 0.f, 0.f, 0.f});
+      else mma_in(c, fr[i], f);
     }
   });
+}
+// before the first use of the sums
+__device__ __forceinline__ void settle(f32x4 (&sacc)[2][2], f32x4 (&pacc)[2][2]) {
+  mma_settle();
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      pin(sacc[rb][nb]);
+      pin(pacc[rb][nb]);
+    }
 }
 
 __device__ __forceinline__ void dkdv_block(const Args& a, int kblk, int head, int batch, char* smem) {
@@ -180,6 +191,7 @@ __device__ __forceinline__ void dkdv_block(const Args& a, int kblk, int head, in
         read_cols<D, 32 * u * D * 2>(lo[i], hi[i], fo.col[i / 2] + (i % 2 ? qo : dO));
       };
       static_for<A>([&](auto ic) { read_t(ic); });
+      settle(sacc, pacc);
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) {
         pin(lv[rb]);
@@ -204,6 +216,8 @@ __device__ __forceinline__ void dkdv_block(const Args& a, int kblk, int head, in
         pb[kb] = frag_acc(p[0], p[1]);
         sb[kb] = frag_acc(d[0], d[1]);
       }
+      mma_ready(pb[0], pb[1]);
+      mma_ready(sb[0], sb[1]);
       static_for<N>([&](auto ic) {
         constexpr int i = decltype(ic)::value, w = i % 2, db = i / 2;
         constexpr int issued = (i + A < N) ? i + A : N;
@@ -212,8 +226,8 @@ __device__ __forceinline__ void dkdv_block(const Args& a, int kblk, int head, in
         pin(f);
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
-          if constexpr (w == 0) dv[kb][db] = mma(f, pb[kb], dv[kb][db]);
-          else dk[kb][db] = mma(f, sb[kb], dk[kb][db]);
+          if constexpr (w == 0) mma_in(dv[kb][db], f, pb[kb]);
+          else mma_in(dk[kb][db], f, sb[kb]);
         }
         if constexpr (i + A < N) read_t(std::integral_constant<int, i + A>{});
       });
@@ -309,6 +323,7 @@ __device__ __forceinline__ void dq_block(const Args& a, int qblk, int head, int 
         constexpr int i = decltype(ic)::value;
         read_cols<D, 32 * u * D * 2>(lo[i], hi[i], fo.col[i] + ko);
       });
+      settle(sacc, pacc);
       bf16x8 sb[2];
 #pragma unroll
       for (int qb = 0; qb < 2; ++qb) {
@@ -326,13 +341,14 @@ __device__ __forceinline__ void dq_block(const Args& a, int qblk, int head, int 
           }
         sb[qb] = frag_acc(d[0], d[1]);
       }
+      mma_ready(sb[0], sb[1]);
       static_for<DB>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
         wait_lgkm<2 * (DB - 1 - i)>();
         bf16x8 f = join(lo[i], hi[i]);
         pin(f);
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) dq[qb][i] = mma(f, sb[qb], dq[qb][i]);
+        for (int qb = 0; qb < 2; ++qb) mma_in(dq[qb][i], f, sb[qb]);
       });
     });
   };

@@ -49,6 +49,18 @@ __device__ __forceinline__ f32x4 mma(const bf16x8& a, const bf16x8& b, f32x4 c) 
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// c += a b in place.  The compiler gives a builtin MFMA's result a register of its
+// own where it likes and hands the old accumulator's to the next LDS read, while
+// the MFMA may still be reading it; in place there is no such register.  It adds
+// no wait states for the result either: mma_settle() goes before the first use
+// by anything but another MFMA.
+__device__ __forceinline__ void mma_in(f32x4& c, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+// (and mma_ready() between the packing of an operand and the first mma_in with it)
+__device__ __forceinline__ void mma_ready(bf16x8& a, bf16x8& b) { asm volatile("s_nop 1" : "+v"(a), "+v"(b)); }
+__device__ __forceinline__ void mma_settle() { asm volatile("s_nop 15" ::: "memory"); }
+
 // max (sum) over the four lanes l, l ^ 16, l ^ 32, l ^ 48, in every lane
 __device__ __forceinline__ float quad_max(float x) {
   const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
