@@ -313,6 +313,24 @@ def test_attention_deterministic_and_causal_bitwise():
     assert not torch.equal(outs[0][t], o2[t])
 
 
+def test_gelu_limits():
+    """The limits and the far tails, where the result is known without rounding,
+    and a relative error for negative u that holds down to the tail."""
+    import torch
+    u = torch.tensor([float("inf"), float("-inf"), float("nan"), 0.0, 3.0e38, -3.0e38, 40.0, -40.0], device="cuda")
+    g = torch.full_like(u, 7.0)
+    T.op_gelu(T.TPS_F32, u.numel(), u, g)
+    assert torch.isnan(g[2])
+    want = torch.tensor([float("inf"), 0.0, 0.0, 3.0e38, 0.0, 40.0, 0.0], device="cuda")
+    assert torch.equal(g[[0, 1, 3, 4, 5, 6, 7]], want)
+    u = torch.linspace(-3.0, 3.0, 1001, device="cuda")
+    g = torch.empty_like(u)
+    T.op_gelu(T.TPS_F32, u.numel(), u, g)
+    ref = 0.5 * u.double() * torch.erfc(-u.double() / 2 ** 0.5)
+    # |u| / 2 times the formula's 1.5e-7, and the f32 roundings of eight operations
+    assert ((g.double() - ref).abs() <= 0.75e-7 * u.abs() + 8 * 2 ** -24 * ref.abs() + 1e-9).all()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_colsum_and_gelu(dtype):
     import torch
