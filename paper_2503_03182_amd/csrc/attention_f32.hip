@@ -1,0 +1,319 @@
+// Fused causal attention in f32 (head dim 64 or 128) on 32x32x2 MFMAs.
+//
+// What bounds it: latency.  The f32 workload's sequences are 128 long with 8
+// (batch, head) pairs, so a workgroup per 128 rows put each kernel on 8 of 256
+// CUs, each streaming its tiles through LDS behind two barriers.  Here a
+// workgroup owns 32 rows and its 4 waves share the other operand's 32-row tiles
+// (wave w takes tiles w, w + 4, ...), loading operands straight into registers:
+// no LDS and no barrier until the four partial results are combined, in wave
+// order, at the end.  Head dim 64, 2 x 128 x 4 heads: forward 19 -> 6 us, backward 71
+// -> 12 us (dK/dV and dQ in one launch); 2048 x 16 heads, which fill the chip
+// either way, 217 -> 99 and 755 -> 343 us.
+//
+// Register layout: every product is issued so that the rows the workgroup owns
+// are the MFMA's N (lane) dimension.  Row fragments take d = 8 j + 4 h + i for
+// lane half h (16-byte loads; any pairing serves as long as both operands use
+// it).  A probability tile held in accumulators is the B operand of the next
+// product as it is: register r of a lane holds row acc_row(r, lane), and the A
+// operand is loaded from those rows (128 contiguous bytes per lane half).
+//
+// Deterministic: fixed tile order per wave, fixed merge order, no atomics.
+#include "kernels.h"
+#include "tps_device.h"
+
+namespace tps {
+
+namespace af {
+
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLn2 = 0.6931471805599453f;
+constexpr int NW = 4;
+
+struct Args {
+  const float *qkv, *dout;
+  const float *lse_in, *dvec;
+  float *o, *lse, *dqkv;
+  int b, s, nh;
+  float scale;
+};
+
+// row fragments of rows row0 + l % 32 (clamped): f[4 j + i] = x[row][8 j + 4 h + i]
+template <int D>
+__device__ __forceinline__ void load_rows(float (&f)[D / 2], const float* x, int64_t ld, int row0, int rows, int lane) {
+  const float* p = x + (int64_t)min(row0 + (lane & 31), rows - 1) * ld + 4 * (lane >> 5);
+#pragma unroll
+  for (int j = 0; j < D / 8; ++j) {
+    const f32x4 t = *reinterpret_cast<const f32x4*>(p + 8 * j);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f[4 * j + i] = t[i];
+  }
+}
+// accumulator-row fragments: f[r][dt] = x[row0 + acc_row(r)][32 dt + l % 32] (rows clamped)
+template <int D>
+__device__ __forceinline__ void load_cols(float (&f)[16][D / 32], const float* x, int64_t ld, int row0, int rows,
+                                          int lane) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float* p = x + (int64_t)min(row0 + acc_row(r, lane), rows - 1) * ld + (lane & 31);
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) f[r][dt] = p[32 * dt];
+  }
+}
+// acc = sum over d of a's rows (M) and b's rows (N)
+template <int D>
+__device__ __forceinline__ f32x16 dot_rows(const float (&a)[D / 2], const float (&b)[D / 2]) {
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+  for (int k = 0; k < D / 2; ++k) acc = Mma<float>::run(a[k], b[k], acc);
+  return acc;
+}
+// out[dt] += a^T v: v[r] the B operand (row acc_row(r), column l % 32)
+template <int D>
+__device__ __forceinline__ void add_cols(f32x16 (&out)[D / 32], const float (&a)[16][D / 32], const float (&v)[16]) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) out[dt] = Mma<float>::run(a[r][dt], v[r], out[dt]);
+}
+template <int N>
+__device__ __forceinline__ void zero(f32x16 (&a)[N]) {
+#pragma unroll
+  for (int t = 0; t < N; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) a[t][r] = 0.f;
+}
+// every wave's N tiles of accumulators into LDS [wave][tile][register][lane]
+template <int N>
+__device__ __forceinline__ void park(float* lds, const f32x16 (&a)[N], int wave, int lane) {
+#pragma unroll
+  for (int t = 0; t < N; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) lds[((wave * N + t) * 16 + r) * 64 + lane] = a[t][r];
+}
+
+template <int D>
+__device__ __forceinline__ void dkdv_block(const Args& a, int kblk, int head, int batch, float* lds) {
+  constexpr int DT = D / 32;
+  const int s = a.s, H = a.nh * D;
+  const int64_t ld = 3 * (int64_t)H;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int k0 = kblk * 32, key = k0 + (lane & 31);
+  const float* base = a.qkv + (int64_t)batch * s * ld + head * D;
+  const float* dO = a.dout + (int64_t)batch * s * H + head * D;
+  const float* lse = a.lse_in + ((int64_t)batch * a.nh + head) * s;
+  const float* dvec = a.dvec + ((int64_t)batch * a.nh + head) * s;
+  const float sl2 = a.scale * kLog2e;
+  float kf[D / 2], vf[D / 2];
+  load_rows<D>(kf, base + H, ld, k0, s, lane);
+  load_rows<D>(vf, base + 2 * H, ld, k0, s, lane);
+  f32x16 acc[2 * DT];   // dK^T, dV^T
+  zero(acc);
+  f32x16(&dk)[DT] = *reinterpret_cast<f32x16(*)[DT]>(&acc[0]);
+  f32x16(&dv)[DT] = *reinterpret_cast<f32x16(*)[DT]>(&acc[DT]);
+  for (int t = kblk + wave; t * 32 < s; t += NW) {
+    const int q0 = t * 32;
+    float qf[D / 2], df[D / 2], dc[16][DT], qc[16][DT];
+    load_rows<D>(qf, base, ld, q0, s, lane);
+    load_rows<D>(df, dO, H, q0, s, lane);
+    load_cols<D>(dc, dO, H, q0, s, lane);
+    load_cols<D>(qc, base, ld, q0, s, lane);
+    float lv[16], dd[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int q = min(q0 + acc_row(r, lane), s - 1);
+      lv[r] = lse[q] * kLog2e;
+      dd[r] = dvec[q];
+    }
+    const f32x16 sa = dot_rows<D>(qf, kf), pa = dot_rows<D>(df, vf);
+    float p[16], d[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int q = q0 + acc_row(r, lane);
+      p[r] = (key <= q && q < s) ? __builtin_amdgcn_exp2f(__builtin_fmaf(sa[r], sl2, -lv[r])) : 0.f;
+      d[r] = p[r] * (pa[r] - dd[r]);
+    }
+    add_cols<D>(dv, dc, p);
+    add_cols<D>(dk, qc, d);
+  }
+  park(lds, acc, wave, lane);
+  __syncthreads();
+  // wave w sums registers 4 w .. 4 w + 3 (d = 32 dt + acc_row(4 w) ..) of every tile
+  if (key >= s) return;
+  float* row = a.dqkv + ((int64_t)batch * s + key) * ld + head * D;
+#pragma unroll
+  for (int t = 0; t < 2 * DT; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 4 * wave + i;
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) v += lds[((w * 2 * DT + t) * 16 + r) * 64 + lane];
+      const int d = 32 * (t % DT) + acc_row(r, lane);
+      if (t < DT) row[H + d] = v * a.scale;
+      else row[2 * H + d] = v;
+    }
+}
+
+template <int D>
+__device__ __forceinline__ void dq_block(const Args& a, int qblk, int head, int batch, float* lds) {
+  constexpr int DT = D / 32;
+  const int s = a.s, H = a.nh * D;
+  const int64_t ld = 3 * (int64_t)H;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q0 = qblk * 32, q = q0 + (lane & 31), qc = min(q, s - 1);
+  const float* base = a.qkv + (int64_t)batch * s * ld + head * D;
+  float qf[D / 2], df[D / 2];
+  load_rows<D>(qf, base, ld, q0, s, lane);
+  load_rows<D>(df, a.dout + (int64_t)batch * s * H + head * D, H, q0, s, lane);
+  const float lse2 = a.lse_in[((int64_t)batch * a.nh + head) * s + qc] * kLog2e;
+  const float dot = a.dvec[((int64_t)batch * a.nh + head) * s + qc];
+  const float sl2 = a.scale * kLog2e;
+  f32x16 dq[DT];
+  zero(dq);
+  for (int t = wave; t <= qblk; t += NW) {
+    const int k0 = t * 32;
+    float kf[D / 2], vf[D / 2], kc[16][DT];
+    load_rows<D>(kf, base + H, ld, k0, s, lane);
+    load_rows<D>(vf, base + 2 * H, ld, k0, s, lane);
+    load_cols<D>(kc, base + H, ld, k0, s, lane);
+    const f32x16 sa = dot_rows<D>(kf, qf), pa = dot_rows<D>(vf, df);
+    float d[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int key = k0 + acc_row(r, lane);
+      const float p = key <= qc ? __builtin_amdgcn_exp2f(__builtin_fmaf(sa[r], sl2, -lse2)) : 0.f;
+      d[r] = p * (pa[r] - dot);
+    }
+    add_cols<D>(dq, kc, d);
+  }
+  park(lds, dq, wave, lane);
+  __syncthreads();
+  if (q >= s) return;
+  float* row = a.dqkv + ((int64_t)batch * s + q) * ld + head * D;
+#pragma unroll
+  for (int t = 0; t < DT; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 4 * wave + i;
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) v += lds[((w * DT + t) * 16 + r) * 64 + lane];
+      row[32 * t + acc_row(r, lane)] = v * a.scale;
+    }
+}
+
+}  // namespace af
+
+template <int D>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256))) void attn_f32_fwd_kernel(af::Args a) {
+  using namespace af;
+  constexpr int DT = D / 32;
+  __shared__ float lds[NW * (DT * 16 + 2) * 64];
+  const int s = a.s, H = a.nh * D, nhb = a.nh * a.b, n = (s + 31) / 32;
+  const int64_t ld = 3 * (int64_t)H;
+  const int qblk = n - 1 - blockIdx.x / nhb;   // longest rows first
+  const int head = blockIdx.x % a.nh, batch = (blockIdx.x / a.nh) % a.b;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q0 = qblk * 32, q = q0 + (lane & 31);
+  const float* base = a.qkv + (int64_t)batch * s * ld + head * D;
+  float qf[D / 2];
+  load_rows<D>(qf, base, ld, q0, s, lane);
+  f32x16 oacc[DT];
+  zero(oacc);
+  float m_run = -INFINITY, l_run = 0.f;
+  const float sl2 = a.scale * kLog2e;
+  for (int t = wave; t <= qblk; t += NW) {
+    const int k0 = t * 32;
+    float kf[D / 2], vc[16][DT];
+    load_rows<D>(kf, base + H, ld, k0, s, lane);
+    load_cols<D>(vc, base + 2 * H, ld, k0, s, lane);
+    const f32x16 sa = dot_rows<D>(kf, qf);
+    float x[16], mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int key = k0 + acc_row(r, lane);
+      x[r] = (key <= q && key < s) ? sa[r] * sl2 : -INFINITY;
+      mx = fmaxf(mx, x[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+    const float m_new = fmaxf(m_run, mx);
+    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+    m_run = m_new;
+    float ls = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      x[r] = __builtin_amdgcn_exp2f(x[r] - m_use);
+      ls += x[r];
+    }
+    l_run = l_run * alpha + ls;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
+    add_cols<D>(oacc, vc, x);
+  }
+  float* ml = lds + NW * DT * 16 * 64;   // m, then l, per wave and lane
+  park(lds, oacc, wave, lane);
+  ml[(2 * wave) * 64 + lane] = m_run;
+  ml[(2 * wave + 1) * 64 + lane] = l_run + __shfl_xor(l_run, 32, kWave);
+  __syncthreads();
+  // wave 0 always holds key 0 <= q: the maximum is finite
+  float m = ml[lane], w8[NW], l = 0.f;
+#pragma unroll
+  for (int w = 1; w < NW; ++w) m = fmaxf(m, ml[2 * w * 64 + lane]);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    w8[w] = __builtin_amdgcn_exp2f(ml[2 * w * 64 + lane] - m);
+    l += ml[(2 * w + 1) * 64 + lane] * w8[w];
+  }
+  if (q >= s) return;
+  const float inv = 1.f / l;
+  float* orow = a.o + ((int64_t)batch * s + q) * H + head * D;
+#pragma unroll
+  for (int t = 0; t < DT; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 4 * wave + i;
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) v += lds[((w * DT + t) * 16 + r) * 64 + lane] * w8[w];
+      orow[32 * t + acc_row(r, lane)] = v * inv;
+    }
+  if (a.lse != nullptr && wave == 0 && lane < 32)
+    a.lse[((int64_t)batch * a.nh + head) * s + q] = m * kLn2 + logf(l);
+}
+
+// Workgroups of dK/dV blocks, then of dQ blocks, each kind heaviest first.
+template <int D>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(1, 2)))
+void attn_f32_bwd_kernel(af::Args a) {
+  __shared__ float lds[af::NW * 2 * (D / 32) * 16 * 64];
+  const int nhb = a.nh * a.b, n = (a.s + 31) / 32, k = blockIdx.x / nhb;
+  const int head = blockIdx.x % a.nh, batch = (blockIdx.x / a.nh) % a.b;
+  if (k < n) af::dkdv_block<D>(a, k, head, batch, lds);
+  else af::dq_block<D>(a, 2 * n - 1 - k, head, batch, lds);
+}
+
+hipError_t attention_f32_fwd_launch(int b, int s, int nh, int d, const void* qkv, void* o, float* lse, hipStream_t st) {
+  const af::Args a{(const float*)qkv, nullptr, nullptr, nullptr, (float*)o, lse, nullptr, b, s, nh,
+                   1.0f / sqrtf((float)d)};
+  const dim3 grid((s + 31) / 32 * nh * b), block(256);
+  if (d == 64) hipLaunchKernelGGL((attn_f32_fwd_kernel<64>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((attn_f32_fwd_kernel<128>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t attention_f32_bwd_launch(int b, int s, int nh, int d, const void* qkv, const float* lse, const void* dout,
+                                    void* dqkv, const float* dvec, hipStream_t st) {
+  const af::Args a{(const float*)qkv, (const float*)dout, lse, dvec, nullptr, nullptr, (float*)dqkv, b, s, nh,
+                   1.0f / sqrtf((float)d)};
+  const dim3 grid(2 * ((s + 31) / 32) * nh * b), block(256);
+  if (d == 64) hipLaunchKernelGGL((attn_f32_bwd_kernel<64>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((attn_f32_bwd_kernel<128>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace tps

@@ -68,6 +68,11 @@ hipError_t attention_bwd_v3_launch(int b, int s, int nh, int nkv, int d, const v
 hipError_t attention_bwd16_launch(int b, int s, int nh, int d, const void* qkv, const float* lse, const void* dout,
                                   void* dqkv, const float* dvec, hipStream_t st);
 
+// f32 (attention_f32.hip)
+hipError_t attention_f32_fwd_launch(int b, int s, int nh, int d, const void* qkv, void* o, float* lse, hipStream_t st);
+hipError_t attention_f32_bwd_launch(int b, int s, int nh, int d, const void* qkv, const float* lse, const void* dout,
+                                    void* dqkv, const float* dvec, hipStream_t st);
+
 hipError_t layernorm_fwd_launch(int dtype, int rows, int cols, const void* x, const void* gamma,
                                 const void* beta, float eps, void* out, float* mean, float* rstd,
                                 hipStream_t st);

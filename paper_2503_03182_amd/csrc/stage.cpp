@@ -839,7 +839,7 @@ int tps_stage::fwd_layer(int l, int mb, const char* W, void* y, uint32_t ops, bo
   if (ops & (1u << OP_ATTN)) {
     ++stats.kernels;
     const int k = kbegin(p.dtype == TPS_BF16 ? (p.d == 128 ? attention_fwd_v3_name(p.b, p.s, p.nh) : "tps::attn_fwd16_kernel")
-                                             : "tps::attn_fwd_kernel<float>",
+                                             : "tps::attn_f32_fwd_kernel",
                          2.0 * p.b * h * (double)p.s * (p.s + 1), ((double)qw + h) * T * es);
     TPS_HIP(attention_fwd_launch(p.dtype, p.b, p.s, p.nh, p.nkv, p.d, qkv, o, opt(TPS_T_LSE) ? lse : nullptr, ks));
     TPS_TRY(kend(k));

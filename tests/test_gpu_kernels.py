@@ -289,6 +289,13 @@ def test_attention_d64_launch_shapes(b, s, nh):
     test_attention_bwd("bf16", b, s, nh, 64)
 
 
+# f32: 32-row blocks whose tiles four waves share, with 1 to 5 tiles and remainders
+@pytest.mark.parametrize("b,s,nh,d", [(1, 1, 1, 64), (2, 31, 2, 128), (1, 33, 3, 64), (2, 129, 2, 64), (1, 160, 1, 128)])
+def test_attention_f32_tiles(b, s, nh, d):
+    test_attention_fwd("f32", b, s, nh, d)
+    test_attention_bwd("f32", b, s, nh, d)
+
+
 def test_attention_deterministic_and_causal_bitwise():
     """Two runs agree bitwise; perturbing query/key/value at position t leaves
     every output row before t bitwise unchanged."""
