@@ -249,9 +249,10 @@ static hipError_t launch_tile(GemmArgs g, hipStream_t stream) {
 }
 
 template <int LAYOUT, int EPI>
-static hipError_t launch_bf16(bool big, const GemmArgs& g, hipStream_t stream) {
-  return big ? launch_quad<LAYOUT, 256, 256, 2, 4, 2, EPI>(g, stream)
-             : launch_quad<LAYOUT, 128, 128, 2, 2, 2, EPI>(g, stream);
+static hipError_t launch_bf16(int bm, const GemmArgs& g, hipStream_t stream) {
+  if (bm == 256) return launch_quad<LAYOUT, 256, 256, 2, 4, 2, EPI>(g, stream);
+  if (bm == 128) return launch_quad<LAYOUT, 128, 128, 2, 2, 2, EPI>(g, stream);
+  return launch_quad<LAYOUT, 64, 128, 2, 2, 2, EPI>(g, stream);
 }
 
 template <int LAYOUT>
@@ -259,22 +260,21 @@ static hipError_t launch_layout(int dtype, GemmArgs g, hipStream_t stream) {
   const GemmTile t = gemm_select_tile(dtype, LAYOUT, g);
   if (t.fast) {
     // the epilogues each layout uses in the stage (others take the generic path)
-    const bool big = t.bm == 256;
     if constexpr (LAYOUT == TPS_GEMM_NT) {
       switch (g.epi) {
-        case TPS_EPI_BIAS: return launch_bf16<LAYOUT, TPS_EPI_BIAS>(big, g, stream);
-        case TPS_EPI_BIAS_RESID: return launch_bf16<LAYOUT, TPS_EPI_BIAS_RESID>(big, g, stream);
-        case TPS_EPI_BIAS_GELU: return launch_bf16<LAYOUT, TPS_EPI_BIAS_GELU>(big, g, stream);
-        case TPS_EPI_GELU_GRAD: return launch_bf16<LAYOUT, TPS_EPI_GELU_GRAD>(big, g, stream);
-        default: return launch_bf16<LAYOUT, TPS_EPI_STORE>(big, g, stream);
+        case TPS_EPI_BIAS: return launch_bf16<LAYOUT, TPS_EPI_BIAS>(t.bm, g, stream);
+        case TPS_EPI_BIAS_RESID: return launch_bf16<LAYOUT, TPS_EPI_BIAS_RESID>(t.bm, g, stream);
+        case TPS_EPI_BIAS_GELU: return launch_bf16<LAYOUT, TPS_EPI_BIAS_GELU>(t.bm, g, stream);
+        case TPS_EPI_GELU_GRAD: return launch_bf16<LAYOUT, TPS_EPI_GELU_GRAD>(t.bm, g, stream);
+        default: return launch_bf16<LAYOUT, TPS_EPI_STORE>(t.bm, g, stream);
       }
     } else if constexpr (LAYOUT == TPS_GEMM_NN) {
-      if (g.epi == TPS_EPI_GELU_GRAD) return launch_bf16<LAYOUT, TPS_EPI_GELU_GRAD>(big, g, stream);
-      if (g.epi == TPS_EPI_BIAS_RESID) return launch_bf16<LAYOUT, TPS_EPI_BIAS_RESID>(big, g, stream);
-      return launch_bf16<LAYOUT, TPS_EPI_STORE>(big, g, stream);
+      if (g.epi == TPS_EPI_GELU_GRAD) return launch_bf16<LAYOUT, TPS_EPI_GELU_GRAD>(t.bm, g, stream);
+      if (g.epi == TPS_EPI_BIAS_RESID) return launch_bf16<LAYOUT, TPS_EPI_BIAS_RESID>(t.bm, g, stream);
+      return launch_bf16<LAYOUT, TPS_EPI_STORE>(t.bm, g, stream);
     } else {
-      if (g.epi == TPS_EPI_ACC_F32) return launch_bf16<LAYOUT, TPS_EPI_ACC_F32>(big, g, stream);
-      return launch_bf16<LAYOUT, TPS_EPI_STORE>(big, g, stream);
+      if (g.epi == TPS_EPI_ACC_F32) return launch_bf16<LAYOUT, TPS_EPI_ACC_F32>(t.bm, g, stream);
+      return launch_bf16<LAYOUT, TPS_EPI_STORE>(t.bm, g, stream);
     }
   }
   if (dtype == TPS_BF16) {

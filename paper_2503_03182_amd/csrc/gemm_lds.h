@@ -83,7 +83,7 @@ struct EpiIn {
 
 // acc: 16 x 16 blocks [2 TA][4]; lane l holds row l % 16 and columns 4 (l / 16)
 // .. +4 of each.  Strip i is blocks 2 i and 2 i + 1 of the wave's rows.
-// row_of(i): output row of row 0 of strip i; col_of(c): output column of
+// row_of(i, r): output row of row r of strip i; col_of(c): output column of
 // column c of the wave's 64 (groups of 8 columns stay together).
 // RAGGED: rows at or past M and groups of 8 columns at or past N (N a multiple
 // of 8) are neither read nor written.
@@ -108,7 +108,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x4 (&acc)[2 
   auto load_strip = [&](int i, EpiIn<EPI, P>& in) {
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-      const int64_t row = row_of(i) + rl0 + q * RPP;
+      const int64_t row = row_of(i, rl0 + q * RPP);
       if constexpr (EPI == TPS_EPI_ACC_F32) {
         if (g.overwrite || !ok(row)) {
           in.c0[q] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -145,7 +145,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x4 (&acc)[2 
       const f32x4 v0 = *reinterpret_cast<const f32x4*>(strip + rl * LDE + cl);
       const f32x4 v1 = *reinterpret_cast<const f32x4*>(strip + rl * LDE + cl + 4);
       const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-      const int64_t row = row_of(i) + rl0 + q * RPP;
+      const int64_t row = row_of(i, rl0 + q * RPP);
       if (!ok(row)) continue;
       if constexpr (EPI == TPS_EPI_ACC_F32) {
         f32x4* c = reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + row * g.ldc + col);

@@ -70,11 +70,13 @@ __device__ __forceinline__ int swz_kc(int r) { return (r >> 1) & 7; }
 //  M/N-contiguous half [k][W columns]: a pass of 32 lanes reads 2 chunks of 8
 //  k-rows, k0 + {0..3} and k0 + 8 + {0..3}.  W = 128 (256-byte rows): the rows'
 //  low bits pick one of 8 chunk pairs; W = 64 (128-byte rows, odd rows in the
-//  other bank half): one of 4.
+//  other bank half): one of 4; W = 32 (64-byte rows, four of them over the
+//  banks): one of 2.
 template <int W>
 __device__ __forceinline__ int swz_mc(int k) {
   if constexpr (W == 128) return ((k & 3) << 2) | (((k >> 3) & 1) << 1);
-  else return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+  else if constexpr (W == 64) return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+  else return ((k >> 3) & 1) << 1;
 }
 
 // Loads of one operand, as halves of R rows (or columns): R / 8 instructions of
@@ -228,7 +230,7 @@ void gemm_quad_kernel(GemmArgs g) {
   constexpr bool A_KC = (LAYOUT != TPS_GEMM_TN), B_KC = (LAYOUT == TPS_GEMM_NT);
   constexpr int NW = WGM * WGN, RA = BM / 2, RB = BN / 2;
   constexpr int TA = RA / WGM / 16, TB = RB / WGN / 16;   // 16-row (column) blocks per wave and half
-  static_assert(TB == 2 && TA % 2 == 0, "epilogue strips of 32 rows, 64 columns per wave");
+  static_assert(TB == 2 && (TA == 1 || TA % 2 == 0), "epilogue strips of 32 rows, 64 columns per wave");
   constexpr int HA = RA * BK * 2, HB = RB * BK * 2;       // bytes of a half
   // LDS: the A halves of every stage, then the B halves
   constexpr int LDS = 2 * S * (HA + HB), BO = 2 * S * HA;
@@ -331,7 +333,18 @@ void gemm_quad_kernel(GemmArgs g) {
     };
     using FH = std::integral_constant<int, F>;
     using XH = std::integral_constant<int, X>;
-    constexpr int RH = NM / 2;   // loads go after the LDS reads, in the second half of a quadrant
+    // the loads of a group go after the LDS reads, in the second half of a
+    // quadrant (what is left after its last MFMA)
+    auto refill = [&](auto mc, auto&& load) {
+      constexpr int m = decltype(mc)::value, RH = NM / 2;
+      if constexpr (REFILL && m >= RH) {
+        if constexpr (m - RH < LPG) load(std::integral_constant<int, m - RH>{});
+        if constexpr (m == NM - 1)
+          static_for<(LPG > NM - RH ? LPG - (NM - RH) : 0)>([&](auto n) {
+            load(std::integral_constant<int, NM - RH + decltype(n)::value>{});
+          });
+      }
+    };
     // ---- quadrant 0 (T, first): T and the first half of this tile are in
     // registers on every wave after the barrier, and its other halves in LDS
     wait_lgkm<0>();
@@ -342,7 +355,7 @@ void gemm_quad_kernel(GemmArgs g) {
     quad(P0{}, FH{}, [&](auto mc) {
       constexpr int m = decltype(mc)::value;
       if constexpr (m < 2 * TB) frb.template read<CB + X * HB, m>(fb[X], cb);
-      if constexpr (REFILL && m >= RH && m < RH + LPG) load1(pc, std::integral_constant<int, m - RH>{}, kt + S, st);
+      refill(mc, [&](auto n) { load1(pc, n, kt + S, st); });
     });
     // ---- quadrant 1 (T, second)
     wait_lgkm<0>();
@@ -362,7 +375,7 @@ void gemm_quad_kernel(GemmArgs g) {
     quad(P1{}, XH{}, [&](auto mc) {
       constexpr int m = decltype(mc)::value;
       if constexpr (NEXT && m < 2 * TA) fra.template read<NA, m>(fa[0], na);
-      if constexpr (REFILL && m >= RH && m < RH + LPG) load2(pc, std::integral_constant<int, m - RH>{}, kt + S, st);
+      refill(mc, [&](auto n) { load2(pc, n, kt + S, st); });
     });
     // ---- quadrant 3 (B, first): the second half's registers take the next
     // tile's first column half (which is this tile's second)
@@ -390,7 +403,11 @@ void gemm_quad_kernel(GemmArgs g) {
     for (int j = 0; j < 2 * TB; ++j) pin(acc[i][j]);
   __syncthreads();   // LDS is reused below
 
-  auto row_of = [&](int i) { return m0 + (i / (TA / 2)) * RA + wm * 16 * TA + (i % (TA / 2)) * 32; };
+  // row r of strip i: 32 rows of T or B, or with one block of 16 per half both
+  auto row_of = [&](int i, int r) {
+    if constexpr (TA == 1) return m0 + (r >> 4) * RA + wm * 16 + (r & 15);
+    else return m0 + (i / (TA / 2)) * RA + wm * 16 * TA + (i % (TA / 2)) * 32 + r;
+  };
   auto col_of = [&](int c) { return B_KC ? n0 + wn * 64 + c : n0 + (c >> 5) * RB + wn * 32 + (c & 31); };
   gemm_epilogue<EPI, RAGGED != 0, NW, TA, LDS>(g, acc, smem, row_of, col_of, lane, wave);
 #endif

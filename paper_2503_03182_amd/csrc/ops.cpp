@@ -256,8 +256,13 @@ GemmTile gemm_select_tile(int dtype, int layout, const GemmArgs& g) {
     // NN contractions), unless padding M and N to them costs more than that
     // (2048 x 4096 x 2048, 512 small tiles: 32 against 40 us; 3000 x 3072 x
     // 3072, 576: 61 against 58 us; 4096 x 4096 x 4096, 1024: 113 against 100 us).
+    // Up to half a workgroup per CU in 128 x 128 tiles, 64 x 128 tiles spread the
+    // product over twice as many (2000 x 1024 x 1024 10.0 -> 7.9 us, 256 x 1024 x 4096
+    // 22 -> 17, TN 1024 x 1024 x 2000 16.5 -> 11.3; past that they lose: 1000 x 4096 x
+    // 1024, 256 tiles, 12.8 -> 14.6, TN 768 x 3072 x 3000, 144 tiles, 22 -> 32).
     const int64_t t256 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
     const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
+    if (t128 <= 128) return {64, 128, 64, 1};
     return t128 > 512 && t256 * 28 <= t128 * 8 ? GemmTile{256, 256, 64, 1} : GemmTile{128, 128, 64, 1};
   }
   const int64_t t = (int64_t)((M + 255) / 256) * ((N + 127) / 128);
@@ -266,22 +271,23 @@ GemmTile gemm_select_tile(int dtype, int layout, const GemmArgs& g) {
 
 const char* gemm_kernel_name(int dtype, int layout, const GemmArgs& g) {
   // [dtype][tile][layout] of the generic and the small f32 kernel, [ragged][tile][layout][epilogue] of the others
-  static char gen[2][2][3][64], fast[3][2][3][6][80];
+  static char gen[2][2][3][64], fast[3][3][3][6][80];
   static std::once_flag once;
   std::call_once(once, [] {
-    for (int l = 0; l < 3; ++l)
+    for (int l = 0; l < 3; ++l) {
       for (int t = 0; t < 2; ++t) {
         snprintf(gen[0][t][l], sizeof(gen[0][t][l]), t ? "tps::gemm_kernel<float, 128, 128, 32, %d>" : "tps::gemm_f32_kernel<%d>", l);
         snprintf(gen[1][t][l], sizeof(gen[1][t][l]), "tps::gemm_kernel<__bf16, %d, 128, 64, %d>", t ? 256 : 128, l);
-        for (int r = 0; r < 3; ++r)
-          for (int e = 0; e < 6; ++e) {
-            snprintf(fast[r][t][l][e], sizeof(fast[r][t][l][e]), "tps::gemm_quad_kernel<%d, %d, %d, 2, %d, %d, %d, %d>", l,
-                     t ? 256 : 128, t ? 256 : 128, t ? 4 : 2, 2, e, r);
-          }
       }
+      for (int t = 0; t < 3; ++t)
+        for (int r = 0; r < 3; ++r)
+          for (int e = 0; e < 6; ++e)
+            snprintf(fast[r][t][l][e], sizeof(fast[r][t][l][e]), "tps::gemm_quad_kernel<%d, %d, %d, 2, %d, 2, %d, %d>", l,
+                     64 << t, t == 2 ? 256 : 128, t == 2 ? 4 : 2, e, r);
+    }
   });
   const GemmTile t = gemm_select_tile(dtype, layout, g);
-  if (t.fast) return fast[g.K % 128 ? 2 : g.M % t.bm || g.N % t.bn ? 1 : 0][t.bm == 256][layout][g.epi];
+  if (t.fast) return fast[g.K % 128 ? 2 : g.M % t.bm || g.N % t.bn ? 1 : 0][t.bm == 256 ? 2 : t.bm == 128][layout][g.epi];
   return gen[dtype == TPS_BF16][t.bm == (dtype == TPS_BF16 ? 256 : 128)][layout];
 }
 

@@ -26,8 +26,8 @@ def _round(a, dtype):
     return synth.round_to_storage(np.asarray(a, dtype=np.float32), dtype).astype(np.float64)
 
 
-# aligned and ragged shapes at both tile sizes of the direct-to-LDS kernel (128 x
-# 128 up to 512 tiles, 256 x 256 past that), with 1, 2, 3, 4 and more K tiles
+# aligned and ragged shapes at the tile sizes of the direct-to-LDS kernel (64 x 128
+# up to 128 tiles of 128 x 128, those up to 512, 256 x 256 past that), with 1, 2, 3, 4 and more K tiles
 # of 64 (the loop takes them in pairs); f32 takes the generic kernel
 GEMM_SHAPES = [(200, 264, 136), (1000, 520, 72), (64, 64, 8), (2072, 4104, 264),
                (256, 384, 192), (4096, 2560, 128), (384, 256, 512), (128, 128, 64), (256, 128, 128),
@@ -56,7 +56,8 @@ def test_gemm_store(dtype, layout, shape):
 
 @pytest.mark.parametrize("layout", [T.GEMM_NT, T.GEMM_NN, T.GEMM_TN])
 @pytest.mark.parametrize("shape", [
-    (8, 8, 8), (136, 120, 64), (120, 136, 1000), (264, 392, 384),      # 128 x 128 tiles
+    (8, 8, 8), (136, 120, 64), (120, 136, 1000), (264, 392, 384),      # 64 x 128 tiles
+    (2056, 1160, 72), (1544, 2312, 384),                               # 128 x 128 tiles
     (2056, 8328, 72), (4104, 4232, 256), (5888, 3080, 520)])           # 256 x 256 tiles
 def test_gemm_ragged_edges(layout, shape):
     """M, N and K that leave part of a tile: nothing outside the operands may
