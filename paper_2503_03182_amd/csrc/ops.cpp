@@ -1,5 +1,6 @@
 // Op-level C ABI (tpstage_ops.h): argument checks, then one kernel launch
 // sequence on the caller's stream.
+#include <algorithm>
 #include <cstdio>
 #include <mutex>
 #include <string>
@@ -228,6 +229,37 @@ static bool fast_epilogue(int layout, int epi) {
 
 static bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// The longest contraction that the direct-to-LDS kernels can take: their tile
+// offsets are 32-bit numbers that stay below 2^31.  An operand with K in its
+// rows reaches K rows from a tile's start, one with K along its rows 256.
+// Ragged products check their loads by offsets past the end too: the rows of
+// the K tiles that pad K to a whole pair, and a partial tile's columns.
+static int64_t gemm_max_k(int layout, const GemmArgs& g) {
+  const bool whole = g.M % 256 == 0 && g.N % 256 == 0 && g.K % 128 == 0;
+  const int64_t lim = int64_t(1) << 31, pad = whole ? 0 : 128, cols = whole ? 0 : 512;
+  const int64_t ra = (lim - cols) / (2 * std::max<int64_t>(g.lda, 1)) - pad;
+  const int64_t rb = (lim - cols) / (2 * std::max<int64_t>(g.ldb, 1)) - pad;
+  int64_t k = lim;
+  if (layout == TPS_GEMM_TN) k = std::min(k, ra);
+  else if (ra < 256) k = 0;
+  if (layout != TPS_GEMM_NT) k = std::min(k, rb);
+  else if (rb < 256) k = 0;
+  return std::max<int64_t>(k, 0);
+}
+
+// K of one launch.  A weight gradient of more tokens than gemm_max_k accumulates
+// over several launches of about equal K (multiples of 128): the product stays
+// on the fast kernels, for one more pass over C each.
+static int gemm_launch_k(int dtype, int layout, const GemmArgs& g) {
+  if (dtype != TPS_BF16 || layout != TPS_GEMM_TN || g.epi != TPS_EPI_ACC_F32) return g.K;
+  const int64_t kmax = gemm_max_k(layout, g) / 128 * 128;
+  if (g.K <= kmax || kmax == 0) return g.K;
+  const int64_t n = (g.K + kmax - 1) / kmax;
+  GemmArgs c = g;
+  c.K = (int)((g.K + n * 128 - 1) / (n * 128) * 128);
+  return gemm_select_tile(dtype, layout, c).fast ? c.K : g.K;
+}
+
 GemmTile gemm_select_tile(int dtype, int layout, const GemmArgs& g) {
   const int M = g.M, N = g.N, K = g.K;
   if (dtype != TPS_BF16) {
@@ -239,16 +271,13 @@ GemmTile gemm_select_tile(int dtype, int layout, const GemmArgs& g) {
   }
   // direct-to-LDS kernels: every operand 16-byte aligned with leading
   // dimensions in whole 16-byte chunks, an epilogue they instantiate, and
-  // tile offsets within the 32 bits of a buffer load (2 GiB leaves room for
-  // the offset that sends a chunk out of range)
+  // operands whose tiles span at most 2 GiB
   bool ok = K > 0 && N % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && fast_epilogue(layout, g.epi) && al16(g.A) &&
             al16(g.B) && al16(g.C) && g.ldc % 8 == 0;
   if (g.epi == TPS_EPI_BIAS || g.epi == TPS_EPI_BIAS_RESID || g.epi == TPS_EPI_BIAS_GELU) ok = ok && al16(g.bias);
   if (g.epi == TPS_EPI_BIAS_RESID) ok = ok && al16(g.resid) && g.ldr % 8 == 0;
   if (g.epi == TPS_EPI_BIAS_GELU || g.epi == TPS_EPI_GELU_GRAD) ok = ok && al16(g.aux) && g.ldaux % 8 == 0;
-  const int64_t lim = int64_t(1) << 31;
-  const int64_t ra = layout == TPS_GEMM_TN ? K : 256, rb = layout == TPS_GEMM_NT ? 256 : K;
-  ok = ok && (ra + 128) * g.lda * 2 + 512 < lim && (rb + 128) * g.ldb * 2 + 512 < lim;
+  ok = ok && K <= gemm_max_k(layout, g);
   if (ok) {
     // 128 x 128 tiles run two workgroups per CU, 256 x 256 tiles one.  While
     // the small tiles fit the chip at once (512) they win, 1.25-2x below half
@@ -286,8 +315,10 @@ const char* gemm_kernel_name(int dtype, int layout, const GemmArgs& g) {
                      64 << t, t == 2 ? 256 : 128, t == 2 ? 4 : 2, e, r);
     }
   });
-  const GemmTile t = gemm_select_tile(dtype, layout, g);
-  if (t.fast) return fast[g.K % 128 ? 2 : g.M % t.bm || g.N % t.bn ? 1 : 0][t.bm == 256 ? 2 : t.bm == 128][layout][g.epi];
+  GemmArgs c = g;
+  c.K = gemm_launch_k(dtype, layout, g);
+  const GemmTile t = gemm_select_tile(dtype, layout, c);
+  if (t.fast) return fast[c.K % 128 ? 2 : g.M % t.bm || g.N % t.bn ? 1 : 0][t.bm == 256 ? 2 : t.bm == 128][layout][g.epi];
   return gen[dtype == TPS_BF16][t.bm == (dtype == TPS_BF16 ? 256 : 128)][layout];
 }
 
@@ -298,7 +329,17 @@ hipError_t gemm_launch(int dtype, int layout, int epi, int M, int N, int K, cons
   GemmArgs g{M, N, K, A, lda, B, ldb, C, ldc, bias, resid, ldr, aux, ldaux, epi, 0, 0, overwrite};
   if (layout == TPS_GEMM_NT) return gemm_launch_nt(dtype, g, stream);
   if (layout == TPS_GEMM_NN) return gemm_launch_nn(dtype, g, stream);
-  return gemm_launch_tn(dtype, g, stream);
+  const int kl = gemm_launch_k(dtype, layout, g);
+  if (kl == K) return gemm_launch_tn(dtype, g, stream);
+  for (int k = 0; k < K; k += kl) {
+    g.K = std::min(kl, K - k);
+    const hipError_t e = gemm_launch_tn(dtype, g, stream);
+    if (e != hipSuccess) return e;
+    g.A = static_cast<const char*>(g.A) + 2 * kl * lda;
+    g.B = static_cast<const char*>(g.B) + 2 * kl * ldb;
+    g.overwrite = 0;
+  }
+  return hipSuccess;
 }
 
 }  // namespace tps

@@ -85,6 +85,27 @@ def test_gemm_ragged_edges(layout, shape):
     assert bool((dC[:, N:] == 7.0).all())
 
 
+@pytest.mark.parametrize("shape", [(256, 256, 1024), (256, 256, 2048), (264, 136, 1000), (264, 136, 2051)])
+def test_gemm_weight_gradient_over_2gib(shape):
+    """Weight gradients whose operands span 2 GiB and more (rows 2 MiB apart, NaN
+    between them): one launch up to there, then K in parts."""
+    import torch
+    M, N, K = shape
+    ld = 1 << 20
+    A, B = _t(55, (K, M), "bf16"), _t(56, (K, N), "bf16")
+
+    def spread(v):
+        t = torch.full((v.shape[0], ld), float("nan"), dtype=torch.bfloat16, device="cuda")
+        t[:, :v.shape[1]] = to_dev(v, "bf16")
+        return t
+    dA, dB = spread(A), spread(B)
+    dC = torch.full((M, N), 3.0, device="cuda")
+    T.op_gemm(T.TPS_BF16, T.GEMM_TN, T.EPI_ACC_F32, M, N, K, dA, ld, dB, ld, dC, N)
+    torch.cuda.synchronize()
+    ref = torch.from_numpy(A).cuda().double().T @ torch.from_numpy(B).cuda().double() + 3.0
+    assert_close(dC.cpu().numpy(), ref.cpu().numpy(), TOL["f32"])
+
+
 @pytest.mark.parametrize("layout", [T.GEMM_NT, T.GEMM_NN, T.GEMM_TN])
 @pytest.mark.parametrize("shape", [(4, 4, 4), (36, 68, 36), (100, 260, 260), (1000, 512, 516)])
 def test_gemm_f32_small_edges(layout, shape):
