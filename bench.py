@@ -37,10 +37,10 @@ def log(*a):
 # Sources each kernel family is compiled from (device code and the headers it
 # includes); counters recorded for a kernel stay valid while these are unchanged.
 KERNEL_SOURCES = {
-    "tps::gemm_bf16_kernel": ("gemm_pipe.h", "gemm_lds.h", "gemm_impl.h", "gemm_nt.hip", "gemm_nn.hip",
+    "tps::gemm_quad_kernel": ("gemm_quad.h", "gemm_lds.h", "gemm_impl.h", "gemm_nt.hip", "gemm_nn.hip",
                               "gemm_tn.hip", "tps_device.h", "kernels.h"),
-    "tps::attn": ("attention.hip", "attention_fwd.hip", "attention_bwd.hip", "attn_tiles.h", "tps_device.h",
-                  "kernels.h"),
+    "tps::attn": ("attention.hip", "attention_fwd.hip", "attention_bwd.hip", "attn_tiles.h", "attention_fwd16.hip",
+                  "attention_bwd16.hip", "attn16.h", "attention_f32.hip", "gemm_lds.h", "tps_device.h", "kernels.h"),
 }
 
 
